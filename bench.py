@@ -68,6 +68,16 @@ def step_pass_bytes(n, m, k, groups, amp=False):
     return tot
 
 
+def three_pass_bytes(n, m, k):
+    """Algorithmic bytes of each pass over a k-wavelength call on the
+    three-pass path (rows, columns with H, rows), one wavelength at a time:
+    only the DOE's Ny rows of the field leave the chip."""
+    ny, nx = (n, n) if np.ndim(n) == 0 else n
+    f, nn = 8.0 * ny * pass_cols(m), 4.0 * ny * nx
+    return {"pass_a_fwd": k * (f + nn), "pass_b_fwd": 0.0, "pass_c": k * 2 * f, "pass_b_inv": 0.0,
+            "pass_a_inv": k * f + (2 * k - 1) * nn}
+
+
 def pass_cols(m):
     return m if np.ndim(m) == 0 else m[1]
 
@@ -78,9 +88,12 @@ def pass_rates(prof, n, m, k):
     group count per call follows from the launch counts of passes A and C."""
     calls = prof["pass_c"][0] / k
     groups = max(1, round(prof["pass_a_fwd"][0] / calls))
-    tot = step_pass_bytes(n, m, k, groups)
+    three = not prof["pass_b_fwd"][0]
+    tot = three_pass_bytes(n, m, k) if three else step_pass_bytes(n, m, k, groups)
     res = {}
     for name, (cnt, ms) in prof.items():
+        if three and not cnt:
+            continue
         b = tot[name] * calls / max(cnt, 1)
         res[name] = {"launches": int(cnt), "avg_ms": round(ms / max(cnt, 1), 4), "alg_bytes": b,
                      "alg_gbs": round(tot[name] * calls / (ms * 1e-3) / 1e9, 1)}
@@ -346,7 +359,7 @@ def other_workloads_measure(api, wl, torch, ctx):
         out = torch.empty((q["n"], q["n"]), dtype=torch.float32, device="cuda")
         ms = _event_ms(torch, lambda: api.psf(h, prob, out=out, ctx=ctx), reps)
         k = len(q["lams"])
-        step = sum(step_pass_bytes(q["n"], q["m"], k, -(-k // min(4, k))).values())
+        step = sum(three_pass_bytes(q["n"], q["m"], k).values())
         res[name] = {"n": q["n"], "m": q["m"], "n_lambda": k, "us_per_call": round(ms * 1e3, 1),
                      "value": round(k * float(q["m"]) ** 2 / (ms * 1e-3) / 1e6, 1),
                      "alg_gbs": round(step / (ms * 1e-3) / 1e9, 1)}

@@ -141,7 +141,8 @@ const char *dop_last_error(void);
 
 /*
  * Create a context on HIP device `device`: uploads the twiddle table
- * (exp(-2 pi i j / 131072), generated in FP64 and rounded to c64, 1 MiB).
+ * (exp(-2 pi i j / 131072), generated in FP64 and rounded to c64, 1 MiB),
+ * followed by re-ordered copies of its entries for some grids (112 KiB).
  * The context owns only that table.  Synchronous.
  */
 dop_status dop_context_create(int device, dop_context **out);
@@ -263,13 +264,15 @@ dop_status dop_upsample_adjoint_rect(dop_context *ctx, int kind, int ncy, int nc
                                      float *grad_coarse, void *stream);
 
 /* ------------------------------------------------------------------------
- * Per-pass timing.  While enabled, every wavelength's five passes are
+ * Per-pass timing.  While enabled, every wavelength's passes are
  * bracketed by HIP events on the stream they run on; dop_profile_read waits
  * for the recorded events and returns, per pass, the launch count and the
  * summed event-to-event time.  Enabling clears the accumulators.  Timing
  * adds one event record between consecutive passes and is off by default.
  * Pass names: "pass_a_fwd", "pass_b_fwd", "pass_c", "pass_b_inv",
- * "pass_a_inv" (the kernels dop::k_pass_*<log2 M>).
+ * "pass_a_inv" (the kernels dop::k_pass_*<log2 M>).  The three-pass paths
+ * (rows, columns with H, rows) report their passes as "pass_a_fwd", "pass_c"
+ * and "pass_a_inv".
  * ---------------------------------------------------------------------- */
 
 #define DOP_NUM_PASSES 5

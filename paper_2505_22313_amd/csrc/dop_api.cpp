@@ -24,7 +24,8 @@ static __device__ __align__(256) unsigned char scratch[DOP_NOALLOC_MAX_BYTES];
 
 struct dop_context {
   int device = 0;
-  float2 *tw = nullptr;  // kTwN complex64 twiddles exp(-2 pi i j / kTwN)
+  float2 *tw = nullptr;  // kTwN complex64 twiddles exp(-2 pi i j / kTwN), then the
+                         // cross twiddles of the three-pass path (kTwTotal in all)
   void *scratch = nullptr;  // device address of `scratch` on this device
   // per-pass timing (off unless enabled)
   std::mutex prof_mu;
@@ -177,6 +178,10 @@ void fill_common(KParams &kp, const dop_context *ctx, const dop_problem *prob, i
   const int mx = grid_cols(prob), my = grid_rows(prob);
   kp.n = prob->n;
   kp.plan = plan_id(mx, my);
+  if (kp.plan >= kTriMinLM && kp.plan <= kTriMaxLM) {
+    kp.tw3 = ctx->tw + tri_tw_offset(kp.plan);
+    kp.pitch3 = tri_pitch(kp.plan, doe_rows(prob));
+  }
   kp.nrows_in = doe_rows(prob);
   kp.p0x = (mx - prob->n) / 2;
   kp.p0y = (my - doe_rows(prob)) / 2;
@@ -242,15 +247,16 @@ dop_status launch_range(const dop_context *cctx, const KParams &kp, int first, i
   return DOP_OK;
 }
 
-// One wavelength of the small-grid path (rows, columns with H, rows); its
+// One wavelength of a three-pass path (rows, columns with H, rows); its
 // passes are timed as pass_a_fwd, pass_c and pass_a_inv.
-static dop_status launch_small_wavelength(const dop_context *cctx, const KParams &kp,
-                                          hipStream_t stream, bool timed) {
+static dop_status launch_three(const dop_context *cctx, const KParams &kp, hipStream_t stream,
+                               bool timed) {
   dop_context *ctx = const_cast<dop_context *>(cctx);
   std::vector<hipEvent_t> ev;
   dop_status s = take_events(ctx, 3, timed, &ev);
   if (s != DOP_OK) return s;
-  const hipError_t e = launch_small(kp, stream, ev.empty() ? nullptr : ev.data());
+  hipEvent_t *evp = ev.empty() ? nullptr : ev.data();
+  const hipError_t e = tri_path(kp) ? launch_tri(kp, stream, evp) : launch_small(kp, stream, evp);
   keep_events(ctx, ev, {0, 2, 4});
   if (e != hipSuccess)
     return fail(DOP_ERR_DEVICE, "kernel launch failed: %s", hipGetErrorString(e));
@@ -258,6 +264,7 @@ static dop_status launch_small_wavelength(const dop_context *cctx, const KParams
 }
 
 dop_status launch(const dop_context *ctx, const KParams &kp, hipStream_t stream) {
+  if (tri_path(kp)) return launch_three(ctx, kp, stream, true);
   return launch_range(ctx, kp, 0, kNumPasses - 1, stream);
 }
 
@@ -303,14 +310,15 @@ dop_status enqueue_psf_range(const dop_context *ctx, const dop_problem *prob, in
     kp.psf = psf;
   };
   for (int k0 = kbeg; k0 < kend;) {
-    const int gk = kend - k0 < g ? kend - k0 : g;
+    int gk = kend - k0 < g ? kend - k0 : g;
+    KParams kp;
+    setup(kp, k0, ws);
+    if (tri_path(kp)) gk = 1;
     if (gk == 1) {
-      KParams kp;
-      setup(kp, k0, ws);
       kp.first = (k0 == 0);
       kp.saved_out = saved_u ? static_cast<float2 *>(saved_u) + (size_t)k0 * nn : nullptr;
-      const dop_status s = small_path(kp.plan)
-                               ? launch_small_wavelength(ctx, kp, stream, timed)
+      const dop_status s = small_path(kp.plan) || tri_path(kp)
+                               ? launch_three(ctx, kp, stream, timed)
                                : launch_range(ctx, kp, 0, kNumPasses - 1, stream, timed);
       if (s != DOP_OK) return s;
     } else {
@@ -318,8 +326,7 @@ dop_status enqueue_psf_range(const dop_context *ctx, const dop_problem *prob, in
       // passes B, C, B' run per field, pass A' adds the gk intensities to
       // the PSF in one read-modify-write (the same sums in the same order
       // as one wavelength at a time)
-      KParams g0;
-      setup(g0, k0, ws);
+      KParams &g0 = kp;
       g0.first = (k0 == 0);
       g0.group = gk;
       for (int q = 0; q < gk; ++q) {
@@ -381,16 +388,20 @@ dop_status dop_context_create(int device, dop_context **out) {
   (void)hipGetDevice(&prev);
   if (hipSetDevice(device) != hipSuccess) return fail(DOP_ERR_DEVICE, "hipSetDevice(%d) failed", device);
   // FP64-generated twiddles, rounded once to complex64.
-  std::vector<float2> host(kTwN);
+  std::vector<float2> host(kTwTotal);
   for (int j = 0; j < kTwN; ++j) {
     const double a = -2.0 * M_PI * (double)j / (double)kTwN;
     host[j] = make_float2((float)std::cos(a), (float)std::sin(a));
   }
+  for (int lm = kTriMinLM; lm <= kTriMaxLM; ++lm)
+    for (int p = 1, l2 = 1 << (lm - 4); p <= 8; ++p)
+      for (int j = 0; j < l2; ++j)
+        host[tri_tw_offset(lm) + (p - 1) * l2 + j] = host[(p * j) << (kTwLog - lm)];
   dop_context *ctx = new dop_context();
   ctx->device = device;
-  hipError_t e = hipMalloc(reinterpret_cast<void **>(&ctx->tw), sizeof(float2) * kTwN);
+  hipError_t e = hipMalloc(reinterpret_cast<void **>(&ctx->tw), sizeof(float2) * kTwTotal);
   if (e == hipSuccess)
-    e = hipMemcpy(ctx->tw, host.data(), sizeof(float2) * kTwN, hipMemcpyHostToDevice);
+    e = hipMemcpy(ctx->tw, host.data(), sizeof(float2) * kTwTotal, hipMemcpyHostToDevice);
   // the no-allocation entry point's scratch on this device (NULL: that entry
   // point reports the failure; everything else works without it)
   if (e == hipSuccess) ctx->scratch = scratch_on_device(device);

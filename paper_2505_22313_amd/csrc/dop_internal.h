@@ -12,6 +12,15 @@ namespace dop {
 constexpr int kTwLog = 17;
 constexpr int kTwN = 1 << kTwLog;
 
+// Grids 2^kTriMinLM .. 2^kTriMaxLM that the three-pass path of a half-filled
+// plane covers.  Behind the shared table the context keeps, per such grid,
+// the path's cross twiddles exp(-2 pi i p j / M) at [p - 1][j], p = 1..8,
+// j < M / 16: M / 2 entries from index tri_tw_offset(log2 M).
+constexpr int kTriMinLM = 12;
+constexpr int kTriMaxLM = 14;
+constexpr int tri_tw_offset(int lm) { return kTwN + (1 << (lm - 1)) - (1 << (kTriMinLM - 1)); }
+constexpr int kTwTotal = tri_tw_offset(kTriMaxLM + 1);
+
 // Wavelengths per group: pass A forms, and pass A' accumulates, up to this
 // many fields (one workspace field each) per launch.
 constexpr int kMaxGroup = 4;
@@ -39,6 +48,8 @@ enum OutMode : int {
 struct KParams {
   float2 *ws;            // My x Mx c64 workspace (row pitch Mx + kRowPad)
   const float2 *tw;      // twiddle table, kTwN entries
+  const float2 *tw3;     // cross twiddles of this grid (three-pass path)
+  int pitch3;            // items from one group of column pairs to the next (three-pass path)
   int n;                 // DOE columns Nx (row length of every N-wide array)
   int plan;              // plan id of the grid (plan_id)
   int nrows_in;          // rows of the padded input that may be nonzero
@@ -104,6 +115,16 @@ constexpr int kSmallMinLM = 4;
 constexpr int kSmallMaxLM = 11;
 bool small_path(int plan);
 hipError_t launch_small(const KParams &p, hipStream_t stream, hipEvent_t *ev);
+
+// Three-pass path of a half-filled plane (three_pass.hip): tri_path(p) says
+// whether the problem set up in p (plan, extents, window) takes it; tri_pitch
+// gives KParams::pitch3 for a number of rows; launch_tri enqueues one
+// wavelength in any input and output mode, with ev[0..3] (if not NULL)
+// recorded before, between and after its passes.  It needs the workspace of
+// one field.
+bool tri_path(const KParams &p);
+int tri_pitch(int plan, int nrows);
+hipError_t launch_tri(const KParams &p, hipStream_t s, hipEvent_t *ev);
 
 // Largest wavelength group the plan supports (1 if pass A' ends in a
 // radix-67 stage), 0 for an unknown plan.

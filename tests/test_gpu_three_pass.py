@@ -1,0 +1,108 @@
+"""The three-pass path of a half-filled plane (square power-of-two grids of
+4096 .. 16384, DOE at most half of each axis, DOE window wanted) against the
+five digit passes: the same DOE placed in the corner of one that is a row and
+a column larger than half the grid, with a zero aperture outside, takes the
+five passes, and propagation does not depend on the placement.  PSF, saved
+fields, gradient and propagated field, at the edges of the tiles: DOEs that
+fill the half plane, one row or column short of it, odd ones, a single point.
+One ragged problem per option is also compared with the FP64 oracle.
+
+Tolerances are the stated ones of the FP32 transforms: fields 1e-5,
+intensities 2e-5 (1e-4 per element), gradients 1e-4.
+"""
+
+import os
+
+import numpy as np
+import pytest
+
+import oracle
+from oracle import asm
+from oracle import upsample as ups
+from paper_2505_22313_amd import workloads as wl
+from _close import FIELD_ELEM, GRAD_ELEM, INTENSITY_ELEM, assert_close
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+asm.WORKERS = min(16, os.cpu_count() or 1)
+
+
+@pytest.fixture(scope="module")
+def api():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2505_22313_amd import api as _api
+    yield _api
+    _api.default_context(0).release_workspaces()
+    torch.cuda.empty_cache()
+
+
+def errors(got, want):
+    """(rel-L2, max error / max) on the device."""
+    d = (got - want).abs()
+    return (float(torch.linalg.vector_norm(d) / torch.linalg.vector_norm(want)),
+            float(d.max() / want.abs().max()))
+
+
+def check(got, want, l2_tol, elem_tol, what):
+    l2, el = errors(got, want)
+    assert l2 <= l2_tol and el <= elem_tol, f"{what}: rel-L2 {l2:.2e}, element {el:.2e}"
+
+
+@pytest.mark.parametrize("m,ny,nx", [
+    (4096, 2048, 2048), (4096, 2047, 2048), (4096, 2048, 2047), (4096, 1, 1), (4096, 3, 1025),
+    (4096, 1501, 257), (8192, 4096, 4096), (8192, 4095, 4093), (8192, 5, 4096),
+    (16384, 8192, 8192), (16384, 8191, 8189), (16384, 9, 700),
+])
+def test_three_pass_equals_five(api, m, ny, nx):
+    gen = torch.Generator(device="cuda").manual_seed(m + ny + nx)
+    lams = np.array([0.45, 0.62])
+    w = np.array([0.7, 1.3], dtype=np.float32)
+    args = (m, 0.5, 900.0, lams, wl.cauchy_index(lams))
+    small = api.Problem((ny, nx), *args, weights=w)
+    by, bx = m // 2 + 1, m // 2 + 1
+    big = api.Problem((by, bx), *args, weights=w)
+    h = torch.rand((ny, nx), generator=gen, device="cuda") * 1.2
+    amp = torch.rand((ny, nx), generator=gen, device="cuda") * 0.5 + 0.5
+    g = torch.randn((ny, nx), generator=gen, device="cuda")
+
+    def embed(t):
+        out = torch.zeros((by, bx), dtype=t.dtype, device="cuda")
+        out[:ny, :nx] = t
+        return out
+
+    psf, fields = api.psf(h, small, amp=amp, save_fields=True)
+    grad = api.psf_backward(h, small, fields, g, amp=amp)
+    u = api.propagate(fields[1], small, k=1)
+    ref, ref_fields = api.psf(embed(h), big, amp=embed(amp), save_fields=True)
+    check(psf, ref[:ny, :nx], 2e-5, INTENSITY_ELEM, "psf")
+    check(fields, ref_fields[:, :ny, :nx], 1e-5, FIELD_ELEM, "fields")
+    ref_grad = api.psf_backward(embed(h), big, ref_fields, embed(g), amp=embed(amp))
+    check(grad, ref_grad[:ny, :nx], 1e-4, GRAD_ELEM, "gradient")
+    ref_u = api.propagate(embed(fields[1]), big, k=1)[:ny, :nx]
+    check(u, ref_u, 1e-5, FIELD_ELEM, "propagated field")
+    assert torch.equal(psf, api.psf(h, small, amp=amp)), "saving the fields changed the PSF"
+
+
+@pytest.mark.parametrize("up,bandlimit,amp", [(1, False, False), (4, False, True), (1, True, True)])
+def test_three_pass_matches_oracle(api, up, bandlimit, amp):
+    ny, nx, m, dx, z = 1204, 1996, 4096, 0.5, -2500.0
+    lams = np.array([0.43, 0.66])
+    rng = np.random.default_rng(7 + up)
+    hc = rng.uniform(0.0, 1.2, (ny // up, nx // up)).astype(np.float32)
+    hf = ups.upsample(hc, up, "nearest") if up > 1 else hc.astype(np.float64)
+    a = rng.uniform(0.3, 1.0, (ny, nx)).astype(np.float32) if amp else None
+    g = rng.standard_normal((ny, nx)).astype(np.float32)
+    nidx = wl.cauchy_index(lams)
+    prob = api.Problem((ny, nx), m, dx, z, lams, nidx, bandlimit=bandlimit, upsample=up)
+    hd = torch.from_numpy(hc).cuda()
+    ad = None if a is None else torch.from_numpy(a).cuda()
+    psf, fields = api.psf(hd, prob, amp=ad, save_fields=True)
+    grad = api.psf_backward(hd, prob, fields, torch.from_numpy(g).cuda(), amp=ad)
+    want = oracle.psf(hf, dx, z, (m, m), lams, nidx, amp=a, bandlimit=bandlimit)
+    assert_close(psf, want, 2e-5, INTENSITY_ELEM, "psf")
+    wg = oracle.psf_backward(hf, dx, z, (m, m), lams, nidx, g, amp=a, bandlimit=bandlimit)
+    if up > 1:
+        wg = ups.upsample_adjoint(wg, up, "nearest")
+    assert_close(grad, wg, 1e-4, GRAD_ELEM, "gradient")
