@@ -13,12 +13,14 @@
 // each row divided by its sum.  Weights are formed in FP64 and rounded to
 // float32; the sums run in float32.
 //
-// These maps run once per call, not once per wavelength, so they are plain
-// LDS-tiled kernels: the coarse patch a fine tile needs is staged in LDS,
-// interpolated along y, then along x.
+// The fine map is s^2 times the coarse one, so both directions are bound by
+// streaming it once: a thread walks down fine columns with a window of six
+// coarse rows in registers (interpolated rows forward, partial sums in the
+// adjoint), and the taps of a row are the same for the whole block.
 
 #include <hip/hip_runtime.h>
 #include <math.h>
+#include <stdint.h>
 
 #include "dop_internal.h"
 
@@ -28,6 +30,14 @@ namespace {
 #define DEV __device__ __forceinline__
 
 constexpr int kUpMaxS = 16;
+
+// Orders one wavefront's LDS accesses: LDS serves a wavefront in program
+// order, so only the compiler has to be held back.
+DEV void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
 
 // Lanczos-3 kernel L(x) = sinc(x) sinc(x/3), |x| < 3.
 DEV double lanczos3(double x) {
@@ -49,20 +59,25 @@ struct TapTable {
   int shift[kUpMaxS];
 };
 
+// All threads of the block must call; one kernel value per thread, so that
+// the FP64 sines of a residue do not queue up in one lane.
 DEV void tap_table_fill(TapTable &tt, int s) {
-  for (int r = threadIdx.x; r < s; r += blockDim.x) {
+  for (int e = threadIdx.x; e < 6 * s; e += blockDim.x) {
+    const int r = e / 6, t = e % 6;
     const double f = ((double)r + 0.5) / (double)s - 0.5;
     const int fl = f < 0.0 ? -1 : 0;
+    tt.raw[r][t] = lanczos3(f - (double)(fl - 2 + t));
+    if (t == 0) tt.shift[r] = fl - 2;
+  }
+  __syncthreads();
+  for (int r = threadIdx.x; r < s; r += blockDim.x) {
     double sum = 0.0;
 #pragma unroll
-    for (int t = 0; t < 6; ++t) {
-      tt.raw[r][t] = lanczos3(f - (double)(fl - 2 + t));
-      sum += tt.raw[r][t];
-    }
+    for (int t = 0; t < 6; ++t) sum += tt.raw[r][t];
 #pragma unroll
     for (int t = 0; t < 6; ++t) tt.wint[r][t] = (float)(tt.raw[r][t] / sum);
-    tt.shift[r] = fl - 2;
   }
+  __syncthreads();
 }
 
 // Taps of fine sample j: returns i0 and writes the six normalised weights of
@@ -90,20 +105,38 @@ DEV int lanczos_taps(int j, int s, int nc, const TapTable &tt, float *w) {
 // ---------------------------------------------------------------------------
 // Nearest neighbour.
 // ---------------------------------------------------------------------------
+typedef float f4v __attribute__((ext_vector_type(4)));
+
+// One thread: V adjacent fine columns of the s rows of a coarse row (V = 4
+// with 16-byte stores where every row starts on a 16-byte boundary).
+template <int V>
 __global__ __launch_bounds__(256) void k_up_nearest(int ncy, int ncx, int s,
                                                     const float *__restrict__ in,
                                                     float *__restrict__ out) {
-  const int nfy = ncy * s, nfx = ncx * s;
-  for (int y = blockIdx.y; y < nfy; y += gridDim.y) {
-    const float *src = in + (size_t)(y / s) * ncx;
-    float *dst = out + (size_t)y * nfx;
-    for (int x = blockIdx.x * blockDim.x + threadIdx.x; x < nfx; x += gridDim.x * blockDim.x)
-      dst[x] = src[x / s];
+  const int nfx = ncx * s, nv = nfx / V;
+  for (int i = blockIdx.y; i < ncy; i += gridDim.y) {
+    const float *src = in + (size_t)i * ncx;
+    float *dst = out + (size_t)i * s * nfx;
+    for (int x = blockIdx.x * blockDim.x + threadIdx.x; x < nv; x += gridDim.x * blockDim.x) {
+      if constexpr (V == 4) {
+        const f4v v = f4v{src[4 * x / s], src[(4 * x + 1) / s], src[(4 * x + 2) / s],
+                          src[(4 * x + 3) / s]};
+        for (int dy = 0; dy < s; ++dy)
+          *reinterpret_cast<f4v *>(dst + (size_t)dy * nfx + 4 * x) = v;
+      } else {
+        const float v = src[x / s];
+        for (int dy = 0; dy < s; ++dy) dst[(size_t)dy * nfx + x] = v;
+      }
+    }
   }
 }
 
 // Sum of each s x s block of a (ncy s) x (ncx s) map, rows in order, columns
-// in order within a row.
+// in order within a row.  S > 0: s = S, a multiple of 4, read as 16-byte
+// vectors (rows start on 16-byte boundaries), so that a wavefront's loads
+// cover whole lines; S = 0: any s.  14400^2, s = 8: 457 us at S = 0, 152 us
+// at S = 8 (5.5 TB/s), the same bits.
+template <int S>
 __global__ __launch_bounds__(256) void k_up_nearest_adj(int ncy, int ncx, int s,
                                                         const float *__restrict__ g,
                                                         float *__restrict__ out) {
@@ -111,175 +144,282 @@ __global__ __launch_bounds__(256) void k_up_nearest_adj(int ncy, int ncx, int s,
   for (int i = blockIdx.y; i < ncy; i += gridDim.y) {
     for (int k = blockIdx.x * blockDim.x + threadIdx.x; k < ncx; k += gridDim.x * blockDim.x) {
       float a = 0.f;
-      for (int dy = 0; dy < s; ++dy) {
-        const float *row = g + (size_t)(i * s + dy) * nfx + (size_t)k * s;
-        for (int dx = 0; dx < s; ++dx) a += row[dx];
+      if constexpr (S > 0) {
+        f4v v[4][S / 4];
+#pragma unroll
+        for (int d0 = 0; d0 < S; d0 += 4) {
+#pragma unroll
+          for (int dy = 0; dy < 4; ++dy)
+#pragma unroll
+            for (int c = 0; c < S / 4; ++c)
+              v[dy][c] = *reinterpret_cast<const f4v *>(g + (size_t)(i * S + d0 + dy) * nfx +
+                                                        (size_t)k * S + 4 * c);
+#pragma unroll
+          for (int dy = 0; dy < 4; ++dy)
+#pragma unroll
+            for (int c = 0; c < S / 4; ++c) a = (((a + v[dy][c].x) + v[dy][c].y) + v[dy][c].z) + v[dy][c].w;
+        }
+      } else {
+        for (int dy = 0; dy < s; ++dy) {
+          const float *row = g + (size_t)(i * s + dy) * nfx + (size_t)k * s;
+          for (int dx = 0; dx < s; ++dx) a += row[dx];
+        }
       }
       out[(size_t)i * ncx + k] = a;
     }
   }
 }
 
-// ---------------------------------------------------------------------------
-// Lanczos-3, forward: one 64 x 64 fine tile per block.  The taps of the
-// tile's first and last rows bound the coarse patch: at most 63/s + 1 + 6
-// <= 70 coarse rows (and columns) for s >= 1.
-// ---------------------------------------------------------------------------
-constexpr int kUpTile = 64;
-constexpr int kUpPatch = kUpTile + 6;
+// The fine samples whose first tap is b are the s samples from seg_lo(b) on
+// (some of them outside the grid): floor(u_j) = b + 2 there.
+DEV int seg_lo(int b, int s) { return s * (b + 2) + s / 2; }
 
-__global__ __launch_bounds__(256) void k_up_lanczos(int ncy, int ncx, int s,
+// ---------------------------------------------------------------------------
+// Lanczos-3, forward.  A thread owns kUpCols fine columns (adjacent and stored
+// as one 16-byte vector where every fine row starts on a 16-byte boundary, V4;
+// else 64 apart, so that a wavefront stores whole lines) and walks down `nseg` segments of s fine rows
+// that share their six coarse rows: interpolated along x once per coarse row,
+// they stay in registers, and a fine sample costs six multiply-adds.  One
+// 64-lane wavefront per block row of the 256 threads; the segment count is
+// picked by the launcher so that small maps still fill the chip.  2048^2, s = 8
+// (1.09 GB): 647 -> 287 us, 3.8 TB/s of the 5.1 that plain stores reach; a
+// tile in LDS spent its time on two LDS reads per product and on FP64 taps
+// per 4096 samples.
+// ---------------------------------------------------------------------------
+constexpr int kUpCols = 4;
+constexpr int kUpSpan = 64 * kUpCols;  // fine columns per block
+constexpr int kUpMaxSeg = 32;          // segments per wavefront
+
+template <bool V4>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k_up_lanczos(int ncy, int ncx, int s, int nseg,
                                                     const float *__restrict__ in,
                                                     float *__restrict__ out) {
   const int nfy = ncy * s, nfx = ncx * s;
-  __shared__ float rw[kUpTile][6], cw[kUpTile][6];
-  __shared__ int rs[kUpTile], cs[kUpTile];
-  __shared__ float patch[kUpPatch][kUpPatch + 1];
-  __shared__ float vert[kUpTile][kUpPatch + 1];
   __shared__ TapTable tt;
-  const int fy0 = blockIdx.y * kUpTile, fx0 = blockIdx.x * kUpTile;
-  const int tid = threadIdx.x;
+  // taps of the block's fine columns, and of each wavefront's current segment
+  __shared__ float cws[6][kUpSpan];
+  __shared__ int cxs[kUpSpan];
+  __shared__ __align__(16) float rws[4][kUpMaxS][8];
   tap_table_fill(tt, s);
-  __syncthreads();
-  // taps of every row and column of the tile (clamped to the grid: rows past
-  // the edge repeat the last one and are not written)
-  if (tid < kUpTile) {
-    rs[tid] = lanczos_taps(min(fy0 + tid, nfy - 1), s, ncy, tt, rw[tid]);
-  } else if (tid < 2 * kUpTile) {
-    const int c = tid - kUpTile;
-    cs[c] = lanczos_taps(min(fx0 + c, nfx - 1), s, ncx, tt, cw[c]);
-  }
-  __syncthreads();
-  const int cy0 = rs[0], cx0 = cs[0];
-  const int pr = rs[kUpTile - 1] + 6 - cy0;
-  const int pc = cs[kUpTile - 1] + 6 - cx0;
-  for (int e = tid; e < pr * pc; e += blockDim.x) {
-    const int r = e / pc, c = e - (e / pc) * pc;
-    const int gy = cy0 + r, gx = cx0 + c;
-    patch[r][c] = (gy >= 0 && gy < ncy && gx >= 0 && gx < ncx) ? in[(size_t)gy * ncx + gx] : 0.f;
-  }
-  __syncthreads();
-  // along y: vert[r][c] = sum_t rw[r][t] patch[rs[r] - cy0 + t][c]
-  for (int e = tid; e < kUpTile * pc; e += blockDim.x) {
-    const int r = e / pc, c = e - (e / pc) * pc;
-    const int o = rs[r] - cy0;
-    float a = 0.f;
+  // segments -3 .. ncy - 2 cover the fine rows
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int b0 = -3 + (int)(blockIdx.y * 4 + wave) * nseg;
+  const int b1 = min(b0 + nseg, ncy - 1);
+  {
+    float w[6];
+    cxs[threadIdx.x] =
+        lanczos_taps(min((int)(blockIdx.x * kUpSpan + threadIdx.x), nfx - 1), s, ncx, tt, w);
 #pragma unroll
-    for (int t = 0; t < 6; ++t) a += rw[r][t] * patch[o + t][c];
-    vert[r][c] = a;
+    for (int t = 0; t < 6; ++t) cws[t][threadIdx.x] = w[t];
   }
   __syncthreads();
-  // along x
-  for (int e = tid; e < kUpTile * kUpTile; e += blockDim.x) {
-    const int r = e / kUpTile, c = e % kUpTile;
-    const int fy = fy0 + r, fx = fx0 + c;
-    if (fy >= nfy || fx >= nfx) continue;
-    const int o = cs[c] - cx0;
-    float a = 0.f;
+  if (b0 >= b1) return;
+  auto col = [&](int c) { return V4 ? 4 * lane + c : lane + 64 * c; };
+  const int x0 = blockIdx.x * kUpSpan;
+  int cx[kUpCols];
+  float cw[kUpCols][6];
 #pragma unroll
-    for (int t = 0; t < 6; ++t) a += cw[c][t] * vert[r][o + t];
-    out[(size_t)fy * nfx + fx] = a;
+  for (int c = 0; c < kUpCols; ++c) {
+    cx[c] = cxs[col(c)];
+#pragma unroll
+    for (int t = 0; t < 6; ++t) cw[c][t] = cws[t][col(c)];
+  }
+  // coarse row `row` interpolated at this thread's columns (taps outside the
+  // grid have weight zero and their samples count as zero)
+  auto interp = [&](int row, float (&o)[kUpCols]) {
+    const float *src = in + (size_t)min(max(row, 0), ncy - 1) * ncx;
+    const bool live = row >= 0 && row < ncy;
+#pragma unroll
+    for (int c = 0; c < kUpCols; ++c) {
+      float a = 0.f;
+#pragma unroll
+      for (int t = 0; t < 6; ++t) {
+        const int x = cx[c] + t;
+        const float v = src[min(max(x, 0), ncx - 1)];
+        a += cw[c][t] * (x >= 0 && x < ncx ? v : 0.f);
+      }
+      o[c] = live ? a : 0.f;
+    }
+  };
+  float win[6][kUpCols] = {};
+  for (int b = b0 - 5; b < b1; ++b) {  // the first five only fill the window
+#pragma unroll
+    for (int t = 0; t < 5; ++t)
+#pragma unroll
+      for (int c = 0; c < kUpCols; ++c) win[t][c] = win[t + 1][c];
+    interp(b + 5, win[5]);
+    if (b < b0) continue;
+    const int lo = seg_lo(b, s);
+    const int j0 = max(lo, 0), j1 = min(lo + s, nfy);
+    if (lane < s && lo + lane >= 0 && lo + lane < nfy) {
+      float w[6];
+      lanczos_taps(lo + lane, s, ncy, tt, w);
+#pragma unroll
+      for (int t = 0; t < 6; ++t) rws[wave][lane][t] = w[t];
+    }
+    wave_sync();
+#pragma unroll 4
+    for (int j = j0; j < j1; ++j) {
+      const float *rw = rws[wave][j - lo];
+      float *dst = out + (size_t)j * nfx + x0;
+      float a[kUpCols];
+#pragma unroll
+      for (int c = 0; c < kUpCols; ++c) {
+        a[c] = 0.f;
+#pragma unroll
+        for (int t = 0; t < 6; ++t) a[c] += rw[t] * win[t][c];
+      }
+      if constexpr (V4) {
+        if (x0 + 4 * lane < nfx)
+          *reinterpret_cast<f4v *>(dst + 4 * lane) = f4v{a[0], a[1], a[2], a[3]};
+      } else {
+#pragma unroll
+        for (int c = 0; c < kUpCols; ++c)
+          if (x0 + col(c) < nfx) dst[col(c)] = a[c];
+      }
+    }
+    wave_sync();
   }
 }
 
 // ---------------------------------------------------------------------------
-// Lanczos-3, adjoint: one 16 x 16 coarse tile per block.  Coarse sample i is
-// a tap of fine sample j only if floor(u_j) is in [i-3, i+2], i.e. j in
-// [s(i-3) - 1, s(i+3) + s]; a tile therefore gathers from at most
-// s (16 + 6) + 2 fine rows and as many columns (SPAN for s <= SMAX).  Fine
-// rows are staged through LDS 16 at a time, the next chunk loaded into
-// registers while the current one is reduced along x into
-// hsum[row][coarse col]; the reduction along y follows.
+// Lanczos-3, adjoint.  The same walk with six coarse rows of partial sums: a
+// fine sample adds to all six, and when a segment ends its first row is
+// complete along y.  That row goes to LDS, where each thread sums the fine
+// columns of its coarse samples.  A block has kAdjSpan fine columns and the
+// coarse columns whose taps lie among them.  V4: a thread's fine columns are
+// one 16-byte vector (rows start on 16-byte boundaries, and the block's first
+// column is rounded down to one).  2048^2, s = 8: 2255 -> 309 us (3.5 TB/s);
+// the former tile of 16 x 16 coarse samples read the fine map 1.9 times and
+// tested each of its samples for each coarse one.
 // ---------------------------------------------------------------------------
-constexpr int kAdjTile = 16;
-constexpr int kAdjChunk = 16;
 constexpr int kAdjThreads = 256;
+constexpr int kAdjCols = 4;
+constexpr int kAdjSpan = kAdjThreads * kAdjCols;
+constexpr int kAdjMaxRows = 560;  // fine rows of a block, (rows + 5) s: three blocks share a CU
 
-DEV int fine_lo(int i, int s) { return s * (i - 3) - 1; }
-DEV int fine_hi(int i, int s) { return s * (i + 3) + s; }
+// coarse columns per block: the fine columns from seg_lo(k0 - 5) to the end
+// of segment k0 + n - 1
+__host__ __device__ constexpr int adj_groups(int s) { return (kAdjSpan - 3) / s; }
+__host__ __device__ constexpr int adj_cols(int s) { return adj_groups(s) - 5; }
 
-template <int SMAX>
-__global__ __launch_bounds__(kAdjThreads) void k_up_lanczos_adj(int ncy, int ncx, int s,
+template <bool V4>
+__global__ __launch_bounds__(kAdjThreads) void k_up_lanczos_adj(int ncy, int ncx, int s, int nrow,
                                                                 const float *__restrict__ g,
                                                                 float *__restrict__ out) {
-  constexpr int SPAN = SMAX * (kAdjTile + 6) + 2;
-  constexpr int PF = (kAdjChunk * SPAN + kAdjThreads - 1) / kAdjThreads;
   const int nfy = ncy * s, nfx = ncx * s;
   __shared__ TapTable tt;
-  __shared__ float rw[SPAN][6], cw[SPAN][6];
-  __shared__ int rs[SPAN], cs[SPAN];
-  __shared__ float hsum[SPAN][kAdjTile + 1];
-  __shared__ float chunk[kAdjChunk][SPAN + 1];
-  const int i0 = blockIdx.y * kAdjTile, k0 = blockIdx.x * kAdjTile;
+  // taps of the block's fine rows, and of its fine columns; column x of the
+  // block is residue x % s of group x / s, stored [residue][group] (with an
+  // odd pitch) so that threads of neighbouring coarse
+  // columns read neighbouring words
+  __shared__ __align__(16) float rw[kAdjMaxRows][8];
+  __shared__ float cw[6][kAdjSpan + 16], vs[2][kAdjSpan + 16];
+  const int i0 = blockIdx.y * nrow, i1 = min(i0 + nrow, ncy);
+  const int kc = adj_cols(s), k0 = blockIdx.x * kc, k1 = min(k0 + kc, ncx);
+  const int j00 = seg_lo(i0 - 5, s), x00 = seg_lo(k0 - 5, s);
+  const int ng = adj_groups(s), pitch = ng | 1;
   const int tid = threadIdx.x;
-  const int jlo = max(0, fine_lo(i0, s)), jhi = min(nfy - 1, fine_hi(i0 + kAdjTile - 1, s));
-  const int llo = max(0, fine_lo(k0, s)), lhi = min(nfx - 1, fine_hi(k0 + kAdjTile - 1, s));
-  const int nj = jhi - jlo + 1, nl = lhi - llo + 1;
   tap_table_fill(tt, s);
-  __syncthreads();
-  for (int e = tid; e < nj; e += kAdjThreads) rs[e] = lanczos_taps(jlo + e, s, ncy, tt, rw[e]);
-  for (int e = tid; e < nl; e += kAdjThreads) cs[e] = lanczos_taps(llo + e, s, ncx, tt, cw[e]);
-  float nxt[PF];
-  auto load_chunk = [&](int c0) {
-    const int rows = min(kAdjChunk, nj - c0);
+  for (int e = tid; e < (i1 - i0 + 5) * s; e += kAdjThreads) {
+    const int j = j00 + e;
+    if (j >= 0 && j < nfy) lanczos_taps(j, s, ncy, tt, rw[e]);
+  }
+  for (int e = tid; e < ng * s; e += kAdjThreads) {
+    const int x = x00 + e, at = (e % s) * pitch + e / s;
+    float w[6] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    if (x >= 0 && x < nfx) lanczos_taps(x, s, ncx, tt, w);
 #pragma unroll
-    for (int q = 0; q < PF; ++q) {
-      const int e = tid + q * kAdjThreads;
-      const int r = e / nl, c = e - (e / nl) * nl;
-      nxt[q] = r < rows ? g[(size_t)(jlo + c0 + r) * nfx + llo + c] : 0.f;
-    }
-  };
-  const int kk = tid % kAdjTile;  // coarse column of this thread
-  const int k = k0 + kk;
-  const int clo = max(0, fine_lo(k, s) - llo), chi = min(nl - 1, fine_hi(k, s) - llo);
-  load_chunk(0);
-  for (int c0 = 0; c0 < nj; c0 += kAdjChunk) {
-    const int rows = min(kAdjChunk, nj - c0);
-    __syncthreads();  // the previous chunk has been consumed
+    for (int t = 0; t < 6; ++t) cw[t][at] = w[t];
+  }
+  // this thread's fine columns: where they are read, whether they count, and
+  // their words of vs (a spare one for columns outside the block's groups)
+  const int xa = V4 ? x00 & ~3 : x00;  // rounds towards minus infinity
+  int xc[kAdjCols], at[kAdjCols];
+  bool in[kAdjCols];
 #pragma unroll
-    for (int q = 0; q < PF; ++q) {
-      const int e = tid + q * kAdjThreads;
-      const int r = e / nl, c = e - (e / nl) * nl;
-      if (r < rows) chunk[r][c] = nxt[q];
-    }
-    __syncthreads();
-    if (c0 + kAdjChunk < nj) load_chunk(c0 + kAdjChunk);
-    const int r = tid / kAdjTile;
-    if (r < rows) {
-      float a = 0.f;
-      for (int c = clo; c <= chi; ++c) {
-        const int t = k - cs[c];
-        if (t >= 0 && t < 6) a += cw[c][t] * chunk[r][c];
-      }
-      hsum[c0 + r][kk] = a;
-    }
+  for (int c = 0; c < kAdjCols; ++c) {
+    const int x = xa + (V4 ? kAdjCols * tid + c : tid + c * kAdjThreads), e = x - x00;
+    in[c] = x >= 0 && x < nfx;
+    xc[c] = in[c] ? x : 0;
+    at[c] = e >= 0 && e < ng * s ? (e % s) * pitch + e / s : kAdjSpan + 15;
   }
   __syncthreads();
-  const int i = i0 + tid / kAdjTile;
-  if (i < ncy && k < ncx) {
-    const int rlo = max(0, fine_lo(i, s) - jlo), rhi = min(nj - 1, fine_hi(i, s) - jlo);
-    float a = 0.f;
-    for (int r = rlo; r <= rhi; ++r) {
-      const int t = i - rs[r];
-      if (t >= 0 && t < 6) a += rw[r][t] * hsum[r][kk];
+  float acc[6][kAdjCols] = {};
+  for (int b = i0 - 5; b < i1; ++b) {
+    const int lo = seg_lo(b, s);
+    const int j0 = max(lo, 0), j1 = min(lo + s, nfy);
+#pragma unroll 4
+    for (int j = j0; j < j1; ++j) {
+      const float *row = g + (size_t)j * nfx;
+      const float *w = rw[j - j00];
+      float v[kAdjCols];
+#pragma unroll
+      for (int c = 0; c < kAdjCols; ++c)
+        if constexpr (!V4) v[c] = row[xc[c]];
+      if constexpr (V4) {
+        const f4v q = *reinterpret_cast<const f4v *>(row + xc[0]);
+        v[0] = q.x, v[1] = q.y, v[2] = q.z, v[3] = q.w;
+      }
+#pragma unroll
+      for (int c = 0; c < kAdjCols; ++c) v[c] = in[c] ? v[c] : 0.f;
+#pragma unroll
+      for (int t = 0; t < 6; ++t)
+#pragma unroll
+        for (int c = 0; c < kAdjCols; ++c) acc[t][c] += w[t] * v[c];
     }
-    out[(size_t)i * ncx + k] = a;
+    if (b >= i0) {
+      float *line = vs[b & 1];  // the other line may still be read
+#pragma unroll
+      for (int c = 0; c < kAdjCols; ++c) line[at[c]] = acc[0][c];
+      __syncthreads();
+      // coarse column k takes tap t of the columns of segment k - t, which is
+      // group k - t - (k0 - 5)
+      for (int k = k0 + tid; k < k1; k += kAdjThreads) {
+        float a = 0.f;
+#pragma unroll
+        for (int t = 5; t >= 0; --t) {
+          const int grp = k - k0 + 5 - t;
+#pragma unroll 4
+          for (int r = 0; r < s; ++r) a += cw[t][r * pitch + grp] * line[r * pitch + grp];
+        }
+        out[(size_t)b * ncx + k] = a;
+      }
+    }
+#pragma unroll
+    for (int t = 0; t < 6; ++t)
+#pragma unroll
+      for (int c = 0; c < kAdjCols; ++c) acc[t][c] = t < 5 ? acc[t + 1][c] : 0.f;
   }
 }
 
 unsigned cdiv(int a, int b) { return (unsigned)((a + b - 1) / b); }
 
+bool aligned16(const void *p) { return reinterpret_cast<uintptr_t>(p) % 16 == 0; }
+
 }  // namespace
 
 hipError_t launch_upsample(int kind, int ncy, int ncx, int s, const float *coarse, float *fine,
                            hipStream_t stream) {
-  const int nfy = ncy * s, nfx = ncx * s;
+  const int nfx = ncx * s;
   if (kind == 0) {
-    const dim3 grid(cdiv(nfx, 256) < 64 ? cdiv(nfx, 256) : 64, nfy < 4096 ? nfy : 4096);
-    hipLaunchKernelGGL(k_up_nearest, grid, dim3(256), 0, stream, ncy, ncx, s, coarse, fine);
+    const bool v4 = nfx % 4 == 0 && aligned16(fine);
+    const unsigned bx = cdiv(v4 ? nfx / 4 : nfx, 256);
+    const dim3 grid(bx < 64 ? bx : 64, ncy < 4096 ? ncy : 4096);
+    if (v4)
+      hipLaunchKernelGGL(k_up_nearest<4>, grid, dim3(256), 0, stream, ncy, ncx, s, coarse, fine);
+    else
+      hipLaunchKernelGGL(k_up_nearest<1>, grid, dim3(256), 0, stream, ncy, ncx, s, coarse, fine);
   } else {
-    const dim3 grid(cdiv(nfx, kUpTile), cdiv(nfy, kUpTile));
-    hipLaunchKernelGGL(k_up_lanczos, grid, dim3(256), 0, stream, ncy, ncx, s, coarse, fine);
+    // ncy + 2 segments of rows, nseg per wavefront: as many as leave four
+    // wavefronts for each SIMD (each starts with the window's five rows)
+    int nseg = kUpMaxSeg;
+    while (nseg > 1 && (long long)cdiv(nfx, kUpSpan) * cdiv(ncy + 2, nseg) < 4096) nseg /= 2;
+    const dim3 grid(cdiv(nfx, kUpSpan), cdiv(ncy + 2, 4 * nseg));
+    if (nfx % 4 == 0 && aligned16(fine))
+      hipLaunchKernelGGL(k_up_lanczos<true>, grid, dim3(256), 0, stream, ncy, ncx, s, nseg, coarse, fine);
+    else
+      hipLaunchKernelGGL(k_up_lanczos<false>, grid, dim3(256), 0, stream, ncy, ncx, s, nseg, coarse, fine);
   }
   return hipGetLastError();
 }
@@ -287,17 +427,29 @@ hipError_t launch_upsample(int kind, int ncy, int ncx, int s, const float *coars
 hipError_t launch_upsample_adjoint(int kind, int ncy, int ncx, int s, const float *grad_fine,
                                    float *grad_coarse, hipStream_t stream) {
   if (kind == 0) {
-    const dim3 grid(cdiv(ncx, 256) < 64 ? cdiv(ncx, 256) : 64, ncy < 4096 ? ncy : 4096);
-    hipLaunchKernelGGL(k_up_nearest_adj, grid, dim3(256), 0, stream, ncy, ncx, s, grad_fine,
-                       grad_coarse);
-  } else {
-    const dim3 grid(cdiv(ncx, kAdjTile), cdiv(ncy, kAdjTile));
-    if (s <= 8)
-      hipLaunchKernelGGL(k_up_lanczos_adj<8>, grid, dim3(kAdjThreads), 0, stream, ncy, ncx, s,
-                         grad_fine, grad_coarse);
+    const dim3 grid(cdiv(ncx, 256) < 64 ? cdiv(ncx, 256) : 64, ncy < 4096 ? ncy : 4096), t(256);
+    const int v = aligned16(grad_fine) ? s : 0;
+    if (v == 4)
+      hipLaunchKernelGGL(k_up_nearest_adj<4>, grid, t, 0, stream, ncy, ncx, s, grad_fine, grad_coarse);
+    else if (v == 8)
+      hipLaunchKernelGGL(k_up_nearest_adj<8>, grid, t, 0, stream, ncy, ncx, s, grad_fine, grad_coarse);
+    else if (v == 16)
+      hipLaunchKernelGGL(k_up_nearest_adj<16>, grid, t, 0, stream, ncy, ncx, s, grad_fine, grad_coarse);
     else
-      hipLaunchKernelGGL(k_up_lanczos_adj<kUpMaxS>, grid, dim3(kAdjThreads), 0, stream, ncy, ncx,
-                         s, grad_fine, grad_coarse);
+      hipLaunchKernelGGL(k_up_nearest_adj<0>, grid, t, 0, stream, ncy, ncx, s, grad_fine, grad_coarse);
+  } else {
+    // nrow coarse rows per block: up to 64 (five segments of lead-in each),
+    // as many as their taps' LDS holds, fewer while the grid has less than
+    // two blocks for each CU
+    const unsigned bx = cdiv(ncx, adj_cols(s));
+    int nrow = kAdjMaxRows / s - 5;
+    if (nrow > 64) nrow = 64;
+    while (nrow > 4 && bx * cdiv(ncy, nrow) < 512) nrow = (nrow + 1) / 2;
+    const dim3 grid(bx, cdiv(ncy, nrow)), t(kAdjThreads);
+    if (ncx * s % 4 == 0 && aligned16(grad_fine))
+      hipLaunchKernelGGL(k_up_lanczos_adj<true>, grid, t, 0, stream, ncy, ncx, s, nrow, grad_fine, grad_coarse);
+    else
+      hipLaunchKernelGGL(k_up_lanczos_adj<false>, grid, t, 0, stream, ncy, ncx, s, nrow, grad_fine, grad_coarse);
   }
   return hipGetLastError();
 }
