@@ -175,22 +175,24 @@ __global__ __launch_bounds__(256) void k_up_nearest_adj(int ncy, int ncx, int s,
 DEV int seg_lo(int b, int s) { return s * (b + 2) + s / 2; }
 
 // ---------------------------------------------------------------------------
-// Lanczos-3, forward.  A thread owns kUpCols fine columns (adjacent and stored
-// as one 16-byte vector where every fine row starts on a 16-byte boundary, V4;
-// else 64 apart, so that a wavefront stores whole lines) and walks down `nseg` segments of s fine rows
-// that share their six coarse rows: interpolated along x once per coarse row,
-// they stay in registers, and a fine sample costs six multiply-adds.  One
-// 64-lane wavefront per block row of the 256 threads; the segment count is
-// picked by the launcher so that small maps still fill the chip.  2048^2, s = 8
-// (1.09 GB): 647 -> 287 us, 3.8 TB/s of the 5.1 that plain stores reach; a
-// tile in LDS spent its time on two LDS reads per product and on FP64 taps
-// per 4096 samples.
+// Lanczos-3, forward.  A block interpolates its coarse rows along x once, into
+// LDS, its four wavefronts taking rows in turn; then each wavefront walks down
+// nseg segments of s fine rows that share their six coarse rows, the window of
+// six in registers, so that a fine sample costs six multiply-adds.  A thread
+// owns kUpCols fine columns (adjacent and stored as one 16-byte vector where
+// every fine row starts on a 16-byte boundary, V4; else 64 apart, so that a
+// wavefront stores whole lines).  The segment count is picked by the launcher
+// so that small maps still fill the chip.  2048^2, s = 8 (1.09 GB): 647 ->
+// 220 us, of the 215 that plain stores take; a tile in LDS spent its time on
+// two LDS reads per product and on FP64 taps per 4096 samples.
 // ---------------------------------------------------------------------------
 constexpr int kUpCols = 4;
 constexpr int kUpSpan = 64 * kUpCols;  // fine columns per block
-constexpr int kUpMaxSeg = 32;          // segments per wavefront
+constexpr int kUpMaxSeg = 4;           // segments per wavefront
 
-template <bool V4>
+// NEAR (V4 and s >= 3): a thread's columns start at one of two neighbouring
+// taps, so seven samples serve them all.
+template <bool V4, bool NEAR>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k_up_lanczos(int ncy, int ncx, int s, int nseg,
                                                     const float *__restrict__ in,
                                                     float *__restrict__ out) {
@@ -200,10 +202,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
   __shared__ float cws[6][kUpSpan];
   __shared__ int cxs[kUpSpan];
   __shared__ __align__(16) float rws[4][kUpMaxS][8];
+  // coarse rows interpolated along x, from the block's first on; [lane][column]
+  __shared__ __align__(16) float hs[4 * kUpMaxSeg + 5][kUpSpan];
   tap_table_fill(tt, s);
   // segments -3 .. ncy - 2 cover the fine rows
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
-  const int b0 = -3 + (int)(blockIdx.y * 4 + wave) * nseg;
+  const int bb = -3 + (int)blockIdx.y * 4 * nseg, b0 = bb + wave * nseg;
   const int b1 = min(b0 + nseg, ncy - 1);
   {
     float w[6];
@@ -213,7 +217,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
     for (int t = 0; t < 6; ++t) cws[t][threadIdx.x] = w[t];
   }
   __syncthreads();
-  if (b0 >= b1) return;
   auto col = [&](int c) { return V4 ? 4 * lane + c : lane + 64 * c; };
   const int x0 = blockIdx.x * kUpSpan;
   int cx[kUpCols];
@@ -229,26 +232,44 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
   auto interp = [&](int row, float (&o)[kUpCols]) {
     const float *src = in + (size_t)min(max(row, 0), ncy - 1) * ncx;
     const bool live = row >= 0 && row < ncy;
+    auto sample = [&](int x) {
+      const float v = src[min(max(x, 0), ncx - 1)];
+      return x >= 0 && x < ncx ? v : 0.f;
+    };
+    float near[7];
+    if constexpr (NEAR) {
+#pragma unroll
+      for (int t = 0; t < 7; ++t) near[t] = sample(cx[0] + t);
+    }
 #pragma unroll
     for (int c = 0; c < kUpCols; ++c) {
       float a = 0.f;
 #pragma unroll
-      for (int t = 0; t < 6; ++t) {
-        const int x = cx[c] + t;
-        const float v = src[min(max(x, 0), ncx - 1)];
-        a += cw[c][t] * (x >= 0 && x < ncx ? v : 0.f);
-      }
+      for (int t = 0; t < 6; ++t)
+        a += cw[c][t] * (!NEAR ? sample(cx[c] + t) : cx[c] == cx[0] ? near[t] : near[t + 1]);
       o[c] = live ? a : 0.f;
     }
   };
-  float win[6][kUpCols] = {};
-  for (int b = b0 - 5; b < b1; ++b) {  // the first five only fill the window
+#pragma unroll 2
+  for (int e = wave; e < 4 * nseg + 5; e += 4) {
+    float o[kUpCols];
+    interp(bb + e, o);
+    *reinterpret_cast<f4v *>(&hs[e][kUpCols * lane]) = f4v{o[0], o[1], o[2], o[3]};
+  }
+  __syncthreads();
+  float win[6][kUpCols];
+  auto row_in = [&](int row, float (&o)[kUpCols]) {
+    const f4v v = *reinterpret_cast<const f4v *>(&hs[row - bb][kUpCols * lane]);
+    o[0] = v.x, o[1] = v.y, o[2] = v.z, o[3] = v.w;
+  };
+#pragma unroll
+  for (int t = 0; t < 5; ++t) row_in(b0 + t, win[t + 1]);
+  for (int b = b0; b < b1; ++b) {
 #pragma unroll
     for (int t = 0; t < 5; ++t)
 #pragma unroll
       for (int c = 0; c < kUpCols; ++c) win[t][c] = win[t + 1][c];
-    interp(b + 5, win[5]);
-    if (b < b0) continue;
+    row_in(b + 5, win[5]);
     const int lo = seg_lo(b, s);
     const int j0 = max(lo, 0), j1 = min(lo + s, nfy);
     if (lane < s && lo + lane >= 0 && lo + lane < nfy) {
@@ -289,7 +310,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
 // columns of its coarse samples.  A block has kAdjSpan fine columns and the
 // coarse columns whose taps lie among them.  V4: a thread's fine columns are
 // one 16-byte vector (rows start on 16-byte boundaries, and the block's first
-// column is rounded down to one).  2048^2, s = 8: 2255 -> 309 us (3.5 TB/s);
+// column is rounded down to one).  2048^2, s = 8: 2255 -> 303 us (3.6 TB/s);
 // the former tile of 16 x 16 coarse samples read the fine map 1.9 times and
 // tested each of its samples for each coarse one.
 // ---------------------------------------------------------------------------
@@ -411,15 +432,16 @@ hipError_t launch_upsample(int kind, int ncy, int ncx, int s, const float *coars
     else
       hipLaunchKernelGGL(k_up_nearest<1>, grid, dim3(256), 0, stream, ncy, ncx, s, coarse, fine);
   } else {
-    // ncy + 2 segments of rows, nseg per wavefront: as many as leave four
-    // wavefronts for each SIMD (each starts with the window's five rows)
+    // ncy + 2 segments of rows, 4 nseg per block (whose LDS starts with five
+    // more rows): fewer while the chip has not four blocks for each CU
     int nseg = kUpMaxSeg;
-    while (nseg > 1 && (long long)cdiv(nfx, kUpSpan) * cdiv(ncy + 2, nseg) < 4096) nseg /= 2;
+    while (nseg > 1 && (long long)cdiv(nfx, kUpSpan) * cdiv(ncy + 2, 4 * nseg) < 1024) nseg /= 2;
     const dim3 grid(cdiv(nfx, kUpSpan), cdiv(ncy + 2, 4 * nseg));
-    if (nfx % 4 == 0 && aligned16(fine))
-      hipLaunchKernelGGL(k_up_lanczos<true>, grid, dim3(256), 0, stream, ncy, ncx, s, nseg, coarse, fine);
-    else
-      hipLaunchKernelGGL(k_up_lanczos<false>, grid, dim3(256), 0, stream, ncy, ncx, s, nseg, coarse, fine);
+    const bool v4 = nfx % 4 == 0 && aligned16(fine);
+    const auto kernel = v4 && s >= 3 ? k_up_lanczos<true, true>
+                        : v4         ? k_up_lanczos<true, false>
+                                     : k_up_lanczos<false, false>;
+    hipLaunchKernelGGL(kernel, grid, dim3(256), 0, stream, ncy, ncx, s, nseg, coarse, fine);
   }
   return hipGetLastError();
 }
