@@ -215,26 +215,40 @@ def propagate(u_in, prob, k=0, ctx=None, out=None):
     return out
 
 
+# Fields up to this size are grouped without asking how much memory is free
+# (four of them are a 65th of the card's): the grids up to 2048 x 2048 run
+# several wavelengths per launch given the fields.
+_SMALL_FIELD = 64 << 20
+
+
+def _grouped_workspace(ctx, stream, nbytes, field, g):
+    """Workspace of nbytes plus g - 1 more fields, or as many of them as can
+    be allocated; returns (workspace, its usable bytes)."""
+    while g > 1:
+        try:
+            return ctx.workspace(nbytes + (g - 1) * field, stream), nbytes + (g - 1) * field
+        except torch.cuda.OutOfMemoryError:
+            g -= 1
+            ctx.group_cap[field] = g  # do not try the larger group again
+    return ctx.workspace(nbytes, stream), nbytes
+
+
 def _psf_workspace(ctx, prob, stream, save_fields, group):
     """Workspace for dop_psf: one field, or room for a group of up to `group`
     wavelengths (the library then reads h and read-modify-writes the PSF once
-    per group) when the fields are not saved and the memory is free."""
+    per group) when the memory is free and, on larger grids, the fields are
+    not saved."""
     field = workspace_size(prob, L.DOP_OP_PSF)
-    g = 1 if save_fields else max(1, min(int(group), prob.k, ctx.group_cap.get(field, 4)))
-    if g > 1:
+    small = field <= _SMALL_FIELD
+    g = 1 if save_fields and not small else max(1, min(int(group), prob.k, ctx.group_cap.get(field, 4)))
+    if g > 1 and not small:
         # what the device could hold: free memory, blocks torch keeps cached,
         # and this stream's workspace (replaced below), less a margin
         free, _ = torch.cuda.mem_get_info(ctx.device)
         spare = torch.cuda.memory_reserved(ctx.device) - torch.cuda.memory_allocated(ctx.device)
         budget = free + spare + ctx.workspace_bytes(stream) - (4 << 30)
         g = max(1, min(g, budget // field))
-    while g > 1:
-        try:
-            return ctx.workspace(g * field, stream), g * field
-        except torch.cuda.OutOfMemoryError:
-            g -= 1
-            ctx.group_cap[field] = g  # do not try the larger group again
-    return ctx.workspace(field, stream), field
+    return _grouped_workspace(ctx, stream, field, field, g)
 
 
 def psf(h, prob, amp=None, save_fields=False, ctx=None, out=None, group=4):
@@ -295,7 +309,10 @@ def psf_backward(h, prob, saved_u, grad_psf, amp=None, ctx=None, out=None):
     _need(out, "out", torch.float32, prob.h_shape, dev)
     stream = _stream_handle(dev)
     nbytes = workspace_size(prob, L.DOP_OP_PSF_BACKWARD)
-    ws = ctx.workspace(nbytes, stream)
+    field = 8 * prob.my * (prob.mx + 16)
+    g = min(prob.k, ctx.group_cap.get(field, 4)) if field <= _SMALL_FIELD else 1
+    # (fields of a group end on a 256-byte boundary before the fine gradient)
+    ws, _ = _grouped_workspace(ctx, stream, nbytes + (256 if g > 1 else 0), field, g)
     check(lib().dop_psf_backward(ctx.handle, prob.ptr(), _ptr(h), _ptr(amp), _ptr(saved_u),
                                  _ptr(grad_psf), _ptr(out), _ptr(ws), ws.numel(),
                                  ctypes.c_void_p(stream)), "dop_psf_backward")

@@ -327,12 +327,15 @@ struct AxisFreq {
   double a2;
   bool inband;
 };
-DEV AxisFreq axis_freq(int k, int m, double inv_md, double flim, const KParams &p) {
+DEV AxisFreq axis_freq(int k, int m, double inv_md, double flim, double lam) {
 #pragma clang fp contract(off)
   const int ks = k < (m >> 1) ? k : k - m;
   const double f = (double)ks * inv_md;
-  const double a = p.lam * f;
+  const double a = lam * f;
   return AxisFreq{a * a, fabs(f) < flim};
+}
+DEV AxisFreq axis_freq(int k, int m, double inv_md, double flim, const KParams &p) {
+  return axis_freq(k, m, inv_md, flim, p.lam);
 }
 
 // (lambda f)^2 of one axis with the band limit folded in: a frequency outside
@@ -346,13 +349,14 @@ DEV double a2_eff(AxisFreq f) { return f.inband ? f.a2 : 2.0; }
 // -z).  The inverse DFT's 1/M^2 is left to the last pass's output constants.
 // Branch-free: cut bins evaluate a harmless dummy root (1 - s is floored at
 // 2^-60, below any propagating 1 - s >= 2^-53) and are replaced by zero.
-DEV float2 transfer(double a2y, double a2x, const KParams &p) {
+DEV float2 transfer(double a2y, double a2x, double zl) {
 #pragma clang fp contract(off)
   const double s = a2y + a2x;
-  const double t = p.zl * sqrt_unit(fmax(1.0 - s, 0x1p-60));
+  const double t = zl * sqrt_unit(fmax(1.0 - s, 0x1p-60));
   const float2 w = cis_turns((float)(t - rint(t)));
   return s < 1.0 ? w : make_float2(0.f, 0.f);
 }
+DEV float2 transfer(double a2y, double a2x, const KParams &p) { return transfer(a2y, a2x, p.zl); }
 
 // Entry q of a per-group constant, selected with constant indices: indexing
 // a kernel-argument array with a run-time value would copy the whole
@@ -365,8 +369,16 @@ DEV T group_value(const T (&a)[kMaxGroup], int q) {
 
 // One wavelength's term of the PSF (Eq. 4) added to an accumulator: acc +
 // w_k |U|^2 with U = w / (My Mx) folded into wk.  Shared by the per-wavelength
-// and the grouped output stages, so that both round alike.
-DEV float psf_add(float acc, float wk, float2 w) { return acc + wk * (w.x * w.x + w.y * w.y); }
+// and the grouped output stages, with the fused operations spelled out, so
+// that all round alike however the compiler arranges the code around it.
+DEV float psf_add(float acc, float wk, float2 w) {
+  return fmaf(wk, fmaf(w.x, w.x, w.y * w.y), acc);
+}
+
+// One wavelength's term of the height gradient: acc + ck Im(g_E conj(E)).
+DEV float grad_add(float acc, float ck, float2 w, float2 e) {
+  return fmaf(ck, fmaf(w.y, e.x, -(w.x * e.y)), acc);
+}
 
 // Element at a 32-bit byte offset from a block-uniform base: the offset is
 // formed in 32-bit arithmetic so the access can take a scalar base plus one

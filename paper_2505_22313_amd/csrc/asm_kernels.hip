@@ -1130,7 +1130,7 @@ DOP_KERNEL(Plan<PID>::TA) void k_pass_a_inv(KParams p) {
       float2 e = doe_phase(o.h[c >> p.up_log2], p.phase_turns);
       if (o.amp) e = cscale(e, *at_byte(o.amp, c * 4u));
       // c_k Im(g_E conj(E)), g_E = w / (My Mx)
-      *at_byte(o.acc, c * 4u) = accv + p.ck_m2 * (w.y * e.x - w.x * e.y);
+      *at_byte(o.acc, c * 4u) = grad_add(accv, p.ck_m2, w, e);
     }
   };
   constexpr int CH = RUNS < 4 ? RUNS : 4;
@@ -1228,14 +1228,15 @@ DOP_KERNEL(Plan<PID>::TA) void k_pass_a_inv(KParams p) {
 
 // ---------------------------------------------------------------------------
 // Small-grid path (square power-of-two M up to 2048), three passes:
-//   S1: M-point DFT over x of each of the N input rows (field formed from h
-//       on the fly, Eq. 1-2), written in natural frequency order;
+//   S1: M-point DFT over x of each of the N input rows (formed on the fly:
+//       DOE field from h, Eq. 1-2, caller's field or adjoint seed), written
+//       in natural frequency order;
 //   S2: for a run of columns, M-point DFT over y (rows >= N are zeros and not
 //       read), times H (Eq. 3), inverse DFT over y; only the rows the output
 //       needs are written back;
 //   S3: inverse M-point DFT over kx of those rows, then the output stage
 //       (|U|^2 accumulated into the PSF with the wavelength weight, Eq. 4,
-//       and the optional saved field).
+//       and the optional saved field; field; or height gradient).
 // A whole row or column fits in a block, so the 2-D FFT takes two sweeps
 // instead of the large path's digit passes, and the column pass touches
 // only the N rows that hold data.  At these sizes the field (<= 32 MiB)
@@ -1310,79 +1311,156 @@ DEV void gather_first(FirstRegs<G, REV> &pre, const LoadF &ld, const int tid, co
   }
 }
 
-// S1 / S3: one tile = RB rows of M points; the row DFT runs along x.
-// IN_PHASE forward (S1) or OUT_PSF inverse (S3, OUTM = OUT_PSF).  S1 (and S2)
-// take the radices smallest first, so that every thread has items in the
+// A wavelength's constants in a group of GR (one: the plain fields).
+template <int GR, class V>
+DEV V pick(const V &one, const V (&g)[kMaxGroup], int q) {
+  return GR == 1 ? one : group_value(g, q);
+}
+
+// S1: one tile = RB rows of M points for each of the group's wavelengths (the
+// batch index of the DFT is wavelength * RB + row); the row DFT runs along x.
+// S1 and S2 take the radices smallest first, so that every thread has items in the
 // first stage, where the inputs' loads and the phase arithmetic sit (2 %
 // faster at 1024^2 and 2048^2); S3 was faster in the natural order.
-template <int LM, bool INV>
-__global__ __launch_bounds__(SmallPlan<LM>::TR) void k_small_rows(KParams p) {
+// GR > 1: up to kMaxGroup wavelengths in one launch.  These launches are
+// latency-bound (5 us of which the arithmetic is a small part), so a launch
+// of four wavelengths costs little more than one.
+template <int LM, int INM, int GR>
+__global__ __launch_bounds__(SmallPlan<LM>::TR * GR) void k_small_rows_fwd(KParams p) {
   using S = SmallPlan<LM>;
-  constexpr int M = S::M, RB = S::RB, T = S::TR;
-  // element (x, r) of the tile at LDS x * RB + r: x fastest across threads
-  using G = Geo<M, RB, RB, 1, T, true>;
-  using FS = FirstStage<G, !INV>;
-  __shared__ float2 lds[M * RB];
+  constexpr int M = S::M, RB = S::RB, T = S::TR * GR;
+  // element (x, b) of the tile: x fastest across threads; wavelengths in
+  // planes of their own
+  using G = Geo<M, RB * GR, GR == 1 ? RB : 1, GR == 1 ? 1 : M, T, true>;
+  using FS = FirstStage<G, true>;
+  __shared__ float2 lds[M * RB * GR];
   __shared__ float2 tw[M];
-  const int nrows = INV ? p.nrows_out : p.nrows_in;
+  const int nrows = p.nrows_in, n = p.n;
   const int ntiles = (nrows + RB - 1) / RB;
-  const int n = p.n;
-  // forward (S1): the DOE field (Eq. 1-2), zero past column n.  Branch-free:
-  // columns past n read column 0 and are replaced by zero; without an
-  // amplitude the amplitude load reads h[0] and is replaced by one.
+  const size_t nn = (size_t)nrows * n;
+  // the DOE field (Eq. 1-2), the caller's field or the adjoint seed, zero
+  // past column n.  Branch-free: columns past n read column 0 and are
+  // replaced by zero, rows past the last read it and are not written; without
+  // an amplitude the amplitude load reads h[0] and is replaced by one.
   const float *amp_src = p.amp ? p.amp : p.h;
-  auto ld_doe = [&](int y0, int x, int r) {
+  auto ld = [&](int y0, int x, int b) {
+    const int q = GR == 1 ? 0 : b / RB, r = GR == 1 ? b : b % RB;
     const bool in = x < n;
-    const int xc = in ? x : 0;
-    const int y = y0 + r;
-    const float hv = p.h[(size_t)(y >> p.up_log2) * p.nh + (xc >> p.up_log2)];
-    const float av = amp_src[p.amp ? (size_t)y * n + xc : 0];
-    const float a = p.amp ? av : 1.f;
-    const float2 v = cscale(doe_phase(hv, p.phase_turns), a);
+    const int xc = in ? x : 0, y = cmin(y0 + r, nrows - 1);
+    const size_t at = (size_t)y * n + xc;
+    float2 v;
+    if constexpr (INM == IN_PHASE) {
+      const float hv = p.h[(size_t)(y >> p.up_log2) * p.nh + (xc >> p.up_log2)];
+      const float av = amp_src[p.amp ? at : 0];
+      v = cscale(doe_phase(hv, pick<GR>(p.phase_turns, p.phase_turns_g, q)), p.amp ? av : 1.f);
+    } else if constexpr (INM == IN_FIELD) {
+      v = p.u_in[at];
+    } else {
+      v = cscale(p.saved_in[q * nn + at], pick<GR>(p.two_wk, p.two_wk_g, q) * p.gpsf[at]);
+    }
     return in ? v : make_float2(0.f, 0.f);
   };
-  // inverse (S3): the spectrum rows left by S2
-  auto ld_ws = [&](int y0, int kx, int r) { return p.ws[(size_t)(y0 + r) * S::PITCH + kx]; };
-  auto gather = [&](int tile, float2 (&pre)[FS::PER][FS::R], int tid) {
-    const int y0 = tile * RB, nb = cmin(RB, nrows - y0);
-    if constexpr (!INV)
-      gather_first<G, true>(pre, [&](int x, int r) { return ld_doe(y0, x, r); }, tid, nb);
-    else
-      gather_first<G, false>(pre, [&](int kx, int r) { return ld_ws(y0, kx, r); }, tid, nb);
+  const int nb = RB * (GR == 1 ? 1 : p.group);
+  auto gather = [&](int tile, FirstRegs<G, true> &pre, int tid) {
+    gather_first<G, true>(pre, [&](int x, int b) { return ld(tile * RB, x, b); }, tid, nb);
   };
   SmallTw<LM, T> twr;
   twr.load(p.tw);
-  float2 pre[FS::PER][FS::R];
+  FirstRegs<G, true> pre;
   if ((int)blockIdx.x < ntiles) gather(blockIdx.x, pre, threadIdx.x);
   twr.put(tw);  // read from the second stage on, after the first's barriers
   for (int tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
     const int tid = loop_tid();
     const int y0 = tile * RB;
-    const int nb = cmin(RB, nrows - y0);
     if (tile != (int)blockIdx.x) {
       __syncthreads();
       gather(tile, pre, tid);
     }
-    if constexpr (!INV) {
-      auto st = [&](int kx, int r, float2 v) { p.ws[(size_t)(y0 + r) * S::PITCH + kx] = v; };
-      dft_tile<G, false, true, SRC_REG, SNK_FN, M>(lds, tw, NoLoad{}, st, pre, tid, nb);
-    } else {
-      // output stage: w is M^2 U (the inverse DFT's 1/M^2 is in the constants)
+    auto st = [&](int kx, int b, float2 v) {
+      const int q = GR == 1 ? 0 : b / RB, y = y0 + (GR == 1 ? b : b % RB);
+      if (RB == 1 || y < nrows) p.ws[q * p.field_elems + (size_t)y * S::PITCH + kx] = v;
+    };
+    dft_tile<G, false, true, SRC_REG, SNK_FN, M>(lds, tw, NoLoad{}, st, pre, tid, nb);
+  }
+}
+
+// S3: the inverse row DFT of the rows left by S2, then the output stage: w is
+// M^2 U (the inverse DFT's 1/M^2 is in the constants).  A group's terms are
+// added in the order and rounding of one wavelength at a time.
+template <int LM, int OUTM, int GR>
+__global__ __launch_bounds__(SmallPlan<LM>::TR * GR) void k_small_rows_inv(KParams p) {
+  using S = SmallPlan<LM>;
+  constexpr int M = S::M, RB = S::RB, T = S::TR * GR;
+  using G = Geo<M, RB * GR, GR == 1 ? RB : 1, GR == 1 ? 1 : M, T, true>;
+  using FS = FirstStage<G, false>;
+  __shared__ float2 lds[M * RB * GR];
+  __shared__ float2 tw[M];
+  const int nrows = p.nrows_out, n = p.n;
+  const int ntiles = (nrows + RB - 1) / RB;
+  const int group = GR == 1 ? 1 : p.group, nb = RB * group;
+  const size_t nn = (size_t)nrows * n;
+  auto gather = [&](int tile, FirstRegs<G, false> &pre, int tid) {
+    auto ld = [&](int kx, int b) {
+      const int q = GR == 1 ? 0 : b / RB, r = GR == 1 ? b : b % RB;
+      return p.ws[q * p.field_elems + (size_t)cmin(tile * RB + r, nrows - 1) * S::PITCH + kx];
+    };
+    gather_first<G, false>(pre, ld, tid, nb);
+  };
+  SmallTw<LM, T> twr;
+  twr.load(p.tw);
+  FirstRegs<G, false> pre;
+  if ((int)blockIdx.x < ntiles) gather(blockIdx.x, pre, threadIdx.x);
+  twr.put(tw);
+  for (int tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
+    const int tid = loop_tid();
+    const int y0 = tile * RB;
+    if (tile != (int)blockIdx.x) {
+      __syncthreads();
+      gather(tile, pre, tid);
+    }
+    // output element of column x of row y; false if it is not wanted
+    auto place = [&](int x, int y, size_t &at) {
+      if (y >= nrows) return false;
+      if (p.full) {
+        const int ys = y + p.p0y, xs = x + p.p0x;
+        at = (size_t)(ys >= M ? ys - M : ys) * M + (xs >= M ? xs - M : xs);
+        return true;
+      }
+      at = (size_t)y * n + x;
+      return x < n;
+    };
+    // wavelength q's term on top of `acc`
+    auto term = [&](float acc, float2 w, int x, int y, size_t at, int q) {
+      if constexpr (OUTM == OUT_PSF) {
+        if (p.saved_out) p.saved_out[q * nn + at] = cscale(w, p.inv_m2);
+        return psf_add(acc, pick<GR>(p.wk_m4, p.wk_m4_g, q), w);
+      } else {
+        float2 e = doe_phase(p.h[(size_t)(y >> p.up_log2) * p.nh + (x >> p.up_log2)],
+                             pick<GR>(p.phase_turns, p.phase_turns_g, q));
+        if (p.amp) e = cscale(e, p.amp[at]);
+        return grad_add(acc, pick<GR>(p.ck_m2, p.ck_m2_g, q), w, e);
+      }
+    };
+    float *sum = OUTM == OUT_PSF ? p.psf : p.grad_h;
+    if constexpr (GR == 1) {
       auto st = [&](int x, int r, float2 w) {
-        const int y = y0 + r;
-        long long idx;
-        if (p.full) {
-          const int ys = y + p.p0y, xs = x + p.p0x;
-          idx = (long long)(ys >= M ? ys - M : ys) * M + (xs >= M ? xs - M : xs);
-        } else {
-          if (x >= n) return;
-          idx = (long long)y * n + x;
-        }
-        const float accv = p.first ? 0.f : p.psf[idx];
-        p.psf[idx] = psf_add(accv, p.wk_m4, w);
-        if (p.saved_out) p.saved_out[idx] = cscale(w, p.inv_m2);
+        size_t at;
+        if (!place(x, y0 + r, at)) return;
+        if constexpr (OUTM == OUT_FIELD) p.u_out[at] = cscale(w, p.inv_m2);
+        else sum[at] = term(p.first ? 0.f : sum[at], w, x, y0 + r, at, 0);
       };
       dft_tile<G, true, false, SRC_REG, SNK_FN, M>(lds, tw, NoLoad{}, st, pre, tid, nb);
+    } else {
+      dft_tile<G, true, false, SRC_REG, SNK_LDS, M>(lds, tw, NoLoad{}, NoStore{}, pre, tid, nb);
+      for (int e = tid; e < M * RB; e += T) {
+        const int x = e % M, r = e / M;
+        size_t at;
+        if (!place(x, y0 + r, at)) continue;
+        float acc = p.first ? 0.f : sum[at];
+        for (int q = 0; q < group; ++q)
+          acc = term(acc, lds[(q * RB + r) * M + x], x, y0 + r, at, q);
+        sum[at] = acc;
+      }
     }
   }
 }
@@ -1392,6 +1470,7 @@ __global__ __launch_bounds__(SmallPlan<LM>::TR) void k_small_rows(KParams p) {
 // C * 8 bytes wide, so 128 / (C * 8) neighbouring tiles share each cache
 // line: tiles go to blocks in the XCD-aware order, which puts neighbours on
 // one XCD and its L2 (at 1024^2 this took the pass from 18.7 to 14.1 us).
+// blockIdx.y: wavelength of the group.
 template <int LM>
 __global__ __launch_bounds__(SmallPlan<LM>::TC) void k_small_cols(KParams p) {
   using S = SmallPlan<LM>;
@@ -1402,12 +1481,16 @@ __global__ __launch_bounds__(SmallPlan<LM>::TC) void k_small_cols(KParams p) {
   __shared__ float2 tw[M];
   __shared__ double a2col[C];
   constexpr int NT = M / C;
+  const int q = blockIdx.y;
+  float2 *const ws = p.ws + q * p.field_elems;
+  const double lam = group_value(p.lam_g, q), zl = group_value(p.zl_g, q);
+  const double flim_x = group_value(p.flim_x_g, q), flim_y = group_value(p.flim_y_g, q);
   auto gather = [&](int tile, float2 (&pre)[FS::PER][FS::R], int tid) {
     const int x0 = xcd_tile(tile, NT) * C;
     // rows at or past nrows_in are zero: read row 0 and replace (branch-free)
     auto ld = [&](int y, int c) {
       const bool in = y < p.nrows_in;
-      const float2 v = p.ws[(size_t)(in ? y : 0) * S::PITCH + x0 + c];
+      const float2 v = ws[(size_t)(in ? y : 0) * S::PITCH + x0 + c];
       return in ? v : make_float2(0.f, 0.f);
     };
     gather_first<G, true>(pre, ld, tid, C);
@@ -1426,14 +1509,14 @@ __global__ __launch_bounds__(SmallPlan<LM>::TC) void k_small_cols(KParams p) {
     }
     // frequency-x data of the tile's columns; read after the forward DFT,
     // whose stage barriers order this write before them
-    for (int c = tid; c < C; c += T) a2col[c] = a2_eff(axis_freq(x0 + c, M, p.inv_mdx, p.flim_x, p));
+    for (int c = tid; c < C; c += T) a2col[c] = a2_eff(axis_freq(x0 + c, M, p.inv_mdx, flim_x, lam));
     dft_tile<G, false, true, SRC_REG, SNK_LDS, M>(lds, tw, NoLoad{}, NoStore{}, pre, tid);
     auto ld_h = [&](int ky, int c) {
-      const double a2y = a2_eff(axis_freq(ky, M, p.inv_mdy, p.flim_y, p));
-      return cmul(lds[ky * SJ + c], transfer(a2y, a2col[c], p));
+      const double a2y = a2_eff(axis_freq(ky, M, p.inv_mdy, flim_y, lam));
+      return cmul(lds[ky * SJ + c], transfer(a2y, a2col[c], zl));
     };
     auto st = [&](int y, int c, float2 v) {
-      if (y < p.nrows_out) p.ws[(size_t)y * S::PITCH + x0 + c] = v;
+      if (y < p.nrows_out) ws[(size_t)y * S::PITCH + x0 + c] = v;
     };
     float2 dummy[1][1];
     dft_tile<G, true, true, SRC_FN, SNK_FN, M>(lds, tw, ld_h, st, dummy, tid);
@@ -1448,14 +1531,32 @@ static hipError_t launch_small_lm(const KParams &p, hipStream_t s, hipEvent_t *e
   auto grid = [](long long tiles) {
     return (unsigned)(tiles < 1 ? 1 : tiles < kMaxBlocks ? tiles : kMaxBlocks);
   };
+  const dim3 gin(grid((p.nrows_in + S::RB - 1) / S::RB)), gout(grid((p.nrows_out + S::RB - 1) / S::RB));
+  const dim3 t1(S::TR), tg(S::TR * kMaxGroup);
   mark(ev, 0, s);
-  hipLaunchKernelGGL((k_small_rows<LM, false>), dim3(grid((p.nrows_in + S::RB - 1) / S::RB)),
-                     dim3(S::TR), 0, s, p);
+  if (p.in_mode == IN_FIELD)
+    hipLaunchKernelGGL((k_small_rows_fwd<LM, IN_FIELD, 1>), gin, t1, 0, s, p);
+  else if (p.in_mode == IN_PHASE && p.group == 1)
+    hipLaunchKernelGGL((k_small_rows_fwd<LM, IN_PHASE, 1>), gin, t1, 0, s, p);
+  else if (p.in_mode == IN_PHASE)
+    hipLaunchKernelGGL((k_small_rows_fwd<LM, IN_PHASE, kMaxGroup>), gin, tg, 0, s, p);
+  else if (p.group == 1)
+    hipLaunchKernelGGL((k_small_rows_fwd<LM, IN_GRAD, 1>), gin, t1, 0, s, p);
+  else
+    hipLaunchKernelGGL((k_small_rows_fwd<LM, IN_GRAD, kMaxGroup>), gin, tg, 0, s, p);
   mark(ev, 1, s);
-  hipLaunchKernelGGL(k_small_cols<LM>, dim3(grid(S::M / S::C)), dim3(S::TC), 0, s, p);
+  hipLaunchKernelGGL(k_small_cols<LM>, dim3(grid(S::M / S::C), p.group), dim3(S::TC), 0, s, p);
   mark(ev, 2, s);
-  hipLaunchKernelGGL((k_small_rows<LM, true>), dim3(grid((p.nrows_out + S::RB - 1) / S::RB)),
-                     dim3(S::TR), 0, s, p);
+  if (p.out_mode == OUT_FIELD)
+    hipLaunchKernelGGL((k_small_rows_inv<LM, OUT_FIELD, 1>), gout, t1, 0, s, p);
+  else if (p.out_mode == OUT_PSF && p.group == 1)
+    hipLaunchKernelGGL((k_small_rows_inv<LM, OUT_PSF, 1>), gout, t1, 0, s, p);
+  else if (p.out_mode == OUT_PSF)
+    hipLaunchKernelGGL((k_small_rows_inv<LM, OUT_PSF, kMaxGroup>), gout, tg, 0, s, p);
+  else if (p.group == 1)
+    hipLaunchKernelGGL((k_small_rows_inv<LM, OUT_GRADH, 1>), gout, t1, 0, s, p);
+  else
+    hipLaunchKernelGGL((k_small_rows_inv<LM, OUT_GRADH, kMaxGroup>), gout, tg, 0, s, p);
   mark(ev, 3, s);
   return hipGetLastError();
 }
@@ -1463,7 +1564,8 @@ static hipError_t launch_small_lm(const KParams &p, hipStream_t s, hipEvent_t *e
 bool small_path(int plan) { return plan >= kSmallMinLM && plan <= kSmallMaxLM; }
 
 hipError_t launch_small(const KParams &p, hipStream_t s, hipEvent_t *ev) {
-  if (p.in_mode != IN_PHASE || p.out_mode != OUT_PSF) return hipErrorInvalidValue;
+  if (p.group < 1 || p.group > kMaxGroup || (p.in_mode == IN_FIELD && p.group != 1))
+    return hipErrorInvalidValue;
   switch (p.plan) {
     case 4: return launch_small_lm<4>(p, s, ev);
     case 5: return launch_small_lm<5>(p, s, ev);
@@ -1619,14 +1721,6 @@ static hipError_t launch_range(const KParams &p, int first, int last, hipStream_
 hipError_t launch_passes(const KParams &p, int first, int last, hipStream_t s, hipEvent_t *ev) {
   if (first < 0 || last >= kNumPasses || first > last) return hipErrorInvalidValue;
   switch (p.plan) {
-    case 4: return launch_range<4>(p, first, last, s, ev);
-    case 5: return launch_range<5>(p, first, last, s, ev);
-    case 6: return launch_range<6>(p, first, last, s, ev);
-    case 7: return launch_range<7>(p, first, last, s, ev);
-    case 8: return launch_range<8>(p, first, last, s, ev);
-    case 9: return launch_range<9>(p, first, last, s, ev);
-    case 10: return launch_range<10>(p, first, last, s, ev);
-    case 11: return launch_range<11>(p, first, last, s, ev);
     case 12: return launch_range<12>(p, first, last, s, ev);
     case 13: return launch_range<13>(p, first, last, s, ev);
     case 14: return launch_range<14>(p, first, last, s, ev);

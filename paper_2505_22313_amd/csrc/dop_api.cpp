@@ -148,16 +148,17 @@ size_t workspace_bytes(const dop_problem *prob) {
   return (size_t)grid_rows(prob) * ((size_t)grid_cols(prob) + kRowPad) * sizeof(float2);
 }
 
-// Byte offset of the fine-grid gradient in a DOP_OP_PSF_BACKWARD workspace
-// (present when the design is upsampled): after the field, 256-byte aligned.
-static size_t fine_grad_offset(const dop_problem *prob) {
-  return (workspace_bytes(prob) + 255) & ~(size_t)255;
+// Byte offset of the fine-grid gradient in a DOP_OP_PSF_BACKWARD workspace of
+// `fields` fields (present when the design is upsampled): after the fields,
+// 256-byte aligned.
+static size_t fine_grad_offset(const dop_problem *prob, int fields = 1) {
+  return ((size_t)fields * workspace_bytes(prob) + 255) & ~(size_t)255;
 }
 
-static size_t workspace_bytes_op(const dop_problem *prob, int op) {
+static size_t workspace_bytes_op(const dop_problem *prob, int op, int fields = 1) {
   if (op == DOP_OP_PSF_BACKWARD && upsample_factor(prob) > 1)
-    return fine_grad_offset(prob) + (size_t)doe_rows(prob) * prob->n * sizeof(float);
-  return workspace_bytes(prob);
+    return fine_grad_offset(prob, fields) + (size_t)doe_rows(prob) * prob->n * sizeof(float);
+  return (size_t)fields * workspace_bytes(prob);
 }
 
 // Band limit of the sampled transfer function (see DOP_BANDLIMIT), formed
@@ -168,6 +169,18 @@ static double band_limit(double lam, double z, int m, double dx) {
 #pragma clang fp contract(off)
   const double t = 2.0 * std::fabs(z) / ((double)m * dx);
   return 1.0 / (lam * std::sqrt(t * t + 1.0));
+}
+
+// Copy one wavelength's constants into entry q of a group's.
+static void set_group_entry(KParams &g, int q, const KParams &one) {
+  g.phase_turns_g[q] = one.phase_turns;
+  g.wk_m4_g[q] = one.wk_m4;
+  g.lam_g[q] = one.lam;
+  g.zl_g[q] = one.zl;
+  g.flim_x_g[q] = one.flim_x;
+  g.flim_y_g[q] = one.flim_y;
+  g.two_wk_g[q] = one.two_wk;
+  g.ck_m2_g[q] = one.ck_m2;
 }
 
 // Fill the per-wavelength kernel parameters shared by every operation.
@@ -203,6 +216,7 @@ void fill_common(KParams &kp, const dop_context *ctx, const dop_problem *prob, i
   kp.ck_m2 = (float)(2.0 * M_PI * (prob->n_index[k] - 1.0) / lam / m2);
   kp.inv_m2 = (float)(1.0 / m2);
   kp.group = 1;
+  set_group_entry(kp, 0, kp);
   kp.field_elems = workspace_bytes(prob) / sizeof(float2);
 }
 
@@ -264,7 +278,7 @@ static dop_status launch_three(const dop_context *cctx, const KParams &kp, hipSt
 }
 
 dop_status launch(const dop_context *ctx, const KParams &kp, hipStream_t stream) {
-  if (tri_path(kp)) return launch_three(ctx, kp, stream, true);
+  if (small_path(kp.plan) || tri_path(kp)) return launch_three(ctx, kp, stream, true);
   return launch_range(ctx, kp, 0, kNumPasses - 1, stream);
 }
 
@@ -278,13 +292,22 @@ dop_status check_ctx_device(const dop_context *ctx) {
 }
 
 int psf_group(const dop_problem *prob, const void *saved_u, size_t ws_bytes) {
-  if (saved_u || small_path(plan_id(grid_cols(prob), grid_rows(prob)))) return 1;
+  const bool small = small_path(plan_id(grid_cols(prob), grid_rows(prob)));
+  if (saved_u && !small) return 1;
   const size_t field = workspace_bytes(prob);
   const int g = plan_max_group(plan_id(grid_cols(prob), grid_rows(prob)));
   const size_t fit = ws_bytes / field;
   int r = prob->n_lambda < g ? prob->n_lambda : g;
   if (fit < (size_t)r) r = (int)fit;
   return r < 1 ? 1 : r;
+}
+
+// Whether passes launched now are timed one by one.
+static bool profiling(const dop_context *cctx, bool timed) {
+  dop_context *ctx = const_cast<dop_context *>(cctx);
+  if (!timed) return false;
+  std::lock_guard<std::mutex> lk(ctx->prof_mu);
+  return ctx->prof_on;
 }
 
 dop_status enqueue_psf(const dop_context *ctx, const dop_problem *prob, const float *h,
@@ -298,7 +321,8 @@ dop_status enqueue_psf_range(const dop_context *ctx, const dop_problem *prob, in
                              const float *h, const float *amp, float *psf, void *saved_u, void *ws,
                              size_t ws_bytes, hipStream_t stream, bool timed) {
   const size_t nn = (size_t)doe_rows(prob) * prob->n;
-  const int g = psf_group(prob, saved_u, ws_bytes);
+  int g = psf_group(prob, saved_u, ws_bytes);
+  if (small_path(plan_id(grid_cols(prob), grid_rows(prob))) && profiling(ctx, timed)) g = 1;
   auto setup = [&](KParams &kp, int k, void *field) {
     fill_common(kp, ctx, prob, k, field);
     kp.in_mode = IN_PHASE;
@@ -313,37 +337,35 @@ dop_status enqueue_psf_range(const dop_context *ctx, const dop_problem *prob, in
     int gk = kend - k0 < g ? kend - k0 : g;
     KParams kp;
     setup(kp, k0, ws);
+    kp.first = (k0 == 0);
+    kp.saved_out = saved_u ? static_cast<float2 *>(saved_u) + (size_t)k0 * nn : nullptr;
     if (tri_path(kp)) gk = 1;
-    if (gk == 1) {
-      kp.first = (k0 == 0);
-      kp.saved_out = saved_u ? static_cast<float2 *>(saved_u) + (size_t)k0 * nn : nullptr;
-      const dop_status s = small_path(kp.plan) || tri_path(kp)
-                               ? launch_three(ctx, kp, stream, timed)
-                               : launch_range(ctx, kp, 0, kNumPasses - 1, stream, timed);
+    kp.group = gk;
+    for (int q = 1; q < gk; ++q) {
+      KParams kq;
+      fill_common(kq, ctx, prob, k0 + q, ws);
+      set_group_entry(kp, q, kq);
+    }
+    if (small_path(kp.plan) || tri_path(kp)) {
+      const dop_status s = launch_three(ctx, kp, stream, timed);
+      if (s != DOP_OK) return s;
+    } else if (gk == 1) {
+      const dop_status s = launch_range(ctx, kp, 0, kNumPasses - 1, stream, timed);
       if (s != DOP_OK) return s;
     } else {
       // a group: pass A forms the gk fields from one read of the heights,
       // passes B, C, B' run per field, pass A' adds the gk intensities to
       // the PSF in one read-modify-write (the same sums in the same order
       // as one wavelength at a time)
-      KParams &g0 = kp;
-      g0.first = (k0 == 0);
-      g0.group = gk;
-      for (int q = 0; q < gk; ++q) {
-        KParams kq;
-        setup(kq, k0 + q, ws);
-        g0.phase_turns_g[q] = kq.phase_turns;
-        g0.wk_m4_g[q] = kq.wk_m4;
-      }
-      dop_status s = launch_range(ctx, g0, 0, 0, stream, timed);
+      dop_status s = launch_range(ctx, kp, 0, 0, stream, timed);
       if (s != DOP_OK) return s;
       for (int q = 0; q < gk; ++q) {
         KParams kq;
-        setup(kq, k0 + q, static_cast<float2 *>(ws) + (size_t)q * g0.field_elems);
+        setup(kq, k0 + q, static_cast<float2 *>(ws) + (size_t)q * kp.field_elems);
         s = launch_range(ctx, kq, 1, 3, stream, timed);
         if (s != DOP_OK) return s;
       }
-      s = launch_range(ctx, g0, kNumPasses - 1, kNumPasses - 1, stream, timed);
+      s = launch_range(ctx, kp, kNumPasses - 1, kNumPasses - 1, stream, timed);
       if (s != DOP_OK) return s;
     }
     k0 += gk;
@@ -639,13 +661,27 @@ dop_status dop_psf_backward(dop_context *ctx, const dop_problem *prob, const flo
   if ((s = check_ctx_device(ctx)) != DOP_OK) return s;
   const size_t nn = (size_t)doe_rows(prob) * prob->n;
   const int up = upsample_factor(prob);
+  // wavelengths per launch: as many as the workspace has fields for on the
+  // small-grid path, else one
+  int g = 1;
+  if (small_path(plan_id(grid_cols(prob), grid_rows(prob))) && !profiling(ctx, true))
+    while (g < kMaxGroup && g < prob->n_lambda &&
+           workspace_bytes_op(prob, DOP_OP_PSF_BACKWARD, g + 1) <= ws_bytes)
+      ++g;
   // with an upsampled design the passes accumulate the n x n fine gradient in
   // the workspace tail; its s x s block sums are the coarse gradient
   float *grad_fine =
-      up > 1 ? reinterpret_cast<float *>(static_cast<char *>(ws) + fine_grad_offset(prob)) : grad_h;
-  for (int k = 0; k < prob->n_lambda; ++k) {
+      up > 1 ? reinterpret_cast<float *>(static_cast<char *>(ws) + fine_grad_offset(prob, g)) : grad_h;
+  for (int k = 0; k < prob->n_lambda; k += g) {
     KParams kp;
     fill_common(kp, ctx, prob, k, ws);
+    kp.group = prob->n_lambda - k < g ? prob->n_lambda - k : g;
+    for (int q = 1; q < kp.group; ++q) {
+      KParams kq;
+      fill_common(kq, ctx, prob, k + q, ws);
+      kq.zl = -kq.zl;
+      set_group_entry(kp, q, kq);
+    }
     kp.in_mode = IN_GRAD;
     kp.out_mode = OUT_GRADH;
     kp.full = 0;
@@ -653,6 +689,7 @@ dop_status dop_psf_backward(dop_context *ctx, const dop_problem *prob, const flo
     kp.first = (k == 0);
     kp.adjoint = 1;
     kp.zl = -kp.zl;  // conj(H) = H at -z (the band limit depends on |z| only)
+    kp.zl_g[0] = kp.zl;
     kp.h = h;
     kp.amp = amp;
     kp.gpsf = grad_psf;

@@ -92,6 +92,10 @@ struct KParams {
   size_t field_elems;    // elements from one field of a group to the next
   double phase_turns_g[kMaxGroup];
   float wk_m4_g[kMaxGroup];
+  // the rest of a wavelength's constants, for the small-grid path's groups
+  // (set for a group of one as well)
+  double lam_g[kMaxGroup], zl_g[kMaxGroup], flim_x_g[kMaxGroup], flim_y_g[kMaxGroup];
+  float two_wk_g[kMaxGroup], ck_m2_g[kMaxGroup];
 };
 
 constexpr int kNumPasses = 5;
@@ -107,10 +111,11 @@ hipError_t launch_passes(const KParams &p, int first, int last, hipStream_t stre
                          hipEvent_t *ev);
 
 // Small-grid path: square power-of-two grids of 2^kSmallMinLM .. 2^kSmallMaxLM
-// points per side run the PSF (IN_PHASE / OUT_PSF only) as three passes:
-// rows, columns with H, rows.  small_path(plan) says whether a plan id is
-// one of them; launch_small enqueues one wavelength's three passes, with
-// ev[0..3] (if not NULL) recorded before, between and after them.
+// points per side run every operation as three passes: rows, columns with H,
+// rows.  small_path(plan) says whether a plan id is one of them; launch_small
+// enqueues the three passes of p.group wavelengths (PSF and gradient; 1 for
+// fields), with ev[0..3] (if not NULL) recorded before, between and after
+// them.
 constexpr int kSmallMinLM = 4;
 constexpr int kSmallMaxLM = 11;
 bool small_path(int plan);

@@ -592,7 +592,7 @@ TRI_KERNEL(Tri<LM>::TROW) void k_tri_rows_inv(KParams p) {
         float2 e = doe_phase(hrow[xc >> p.up_log2], p.phase_turns);
         if (arow) e = cscale(e, arow[xc]);
         const float2 w = value(t);
-        acc[t] += p.ck_m2 * (w.y * e.x - w.x * e.y);
+        acc[t] = grad_add(acc[t], p.ck_m2, w, e);
       }
     } else if constexpr (OUTM == OUT_PSF) {
 #pragma unroll

@@ -1,0 +1,80 @@
+"""Wavelength groups of the small grids (square powers of two up to 2048):
+several wavelengths per launch give bitwise what one at a time gives, with
+and without saved fields, for the PSF and the gradient, on DOEs that end
+inside a tile of rows and on group sizes of one to four with a rest; and the
+field and gradient modes of the three-pass path against the FP64 oracle
+(fields 1e-5, intensities 2e-5, gradients 1e-4)."""
+
+import os
+
+import numpy as np
+import pytest
+
+import oracle
+from oracle import asm
+from paper_2505_22313_amd import workloads as wl
+from _close import FIELD_ELEM, GRAD_ELEM, INTENSITY_ELEM, assert_close
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+asm.WORKERS = min(16, os.cpu_count() or 1)
+
+
+@pytest.fixture(scope="module")
+def api():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2505_22313_amd import api as _api
+    return _api
+
+
+@pytest.mark.parametrize("m,ny,nx,k,up,amp", [
+    (16, 7, 16, 3, 1, False), (32, 16, 15, 2, 1, True), (64, 33, 20, 5, 1, False),
+    (128, 64, 64, 4, 2, True), (256, 129, 100, 7, 1, False), (512, 500, 512, 3, 4, True),
+    (1024, 513, 512, 2, 1, True), (2048, 1023, 1025, 6, 1, False),
+])
+def test_group_is_bitwise_and_matches_oracle(api, m, ny, nx, k, up, amp):
+    rng = np.random.default_rng(m + k)
+    lams = np.linspace(0.42, 0.68, k)
+    w = np.linspace(0.5, 1.5, k).astype(np.float32)
+    nidx = wl.cauchy_index(lams)
+    dx, z = 0.5, 400.0
+    prob = api.Problem((ny, nx), m, dx, z, lams, nidx, weights=w, upsample=up)
+    hc = rng.uniform(0.0, 1.2, prob.h_shape).astype(np.float32)
+    h = torch.from_numpy(hc).cuda()
+    a = rng.uniform(0.3, 1.0, (ny, nx)).astype(np.float32) if amp else None
+    ad = None if a is None else torch.from_numpy(a).cuda()
+    gn = rng.standard_normal((ny, nx)).astype(np.float32)
+    g = torch.from_numpy(gn).cuda()
+    ctx = api.default_context(0)
+    psf, fields = api.psf(h, prob, amp=ad, save_fields=True)
+    grad = api.psf_backward(h, prob, fields, g, amp=ad)
+    plain = api.psf(h, prob, amp=ad)
+    one = api.psf(h, prob, amp=ad, group=1)
+    ctx.profile_enable(True)  # timed passes run one wavelength at a time
+    psf1, fields1 = api.psf(h, prob, amp=ad, save_fields=True)
+    grad1 = api.psf_backward(h, prob, fields1, g, amp=ad)
+    launches = ctx.profile_read()["pass_c"][0]
+    ctx.profile_enable(False)
+    assert launches == 2 * k
+    assert torch.equal(psf, psf1) and torch.equal(psf, plain) and torch.equal(psf, one)
+    assert torch.equal(fields, fields1) and torch.equal(grad, grad1)
+    hf = np.repeat(np.repeat(hc, up, axis=0), up, axis=1)
+    want, wf = oracle.psf(hf, dx, z, m, lams, nidx, weights=w, amp=a, return_fields=True)
+    assert_close(psf, want, 2e-5, INTENSITY_ELEM, "psf")
+    assert_close(fields[k - 1], wf[k - 1], 1e-5, FIELD_ELEM, "field")
+    wg = oracle.psf_backward(hf, dx, z, m, lams, nidx, gn, weights=w, amp=a)
+    wg = wg.reshape(ny // up, up, nx // up, up).sum((1, 3))
+    assert_close(grad, wg, 1e-4, GRAD_ELEM, "gradient")
+
+
+@pytest.mark.parametrize("mode", ["crop", "full"])
+@pytest.mark.parametrize("m,ny,nx", [(16, 16, 3), (128, 65, 128), (1024, 1, 700), (2048, 2048, 2047)])
+def test_field_matches_oracle(api, m, ny, nx, mode):
+    rng = np.random.default_rng(m + ny)
+    u = (rng.standard_normal((ny, nx)) + 1j * rng.standard_normal((ny, nx))).astype(np.complex64)
+    prob = api.Problem((ny, nx), m, 0.5, -700.0, [0.55], [1.46], out_mode=mode)
+    got = api.propagate(torch.from_numpy(u).cuda(), prob)
+    want = oracle.propagate(u, m, 0.5, 0.55, -700.0, out_mode=mode)
+    assert_close(got, want, 1e-5, FIELD_ELEM, "field")
