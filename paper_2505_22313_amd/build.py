@@ -13,7 +13,7 @@ ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 LIB = os.path.join(PKG, "libdop.so")
 
-SOURCES = ["asm_kernels.hip", "three_pass.hip", "upsample_kernels.hip", "probe_kernels.hip", "dop_api.cpp",
+SOURCES = ["asm_kernels.hip", "three_pass.hip", "small_grid.hip", "upsample_kernels.hip", "probe_kernels.hip", "dop_api.cpp",
            "dop_serve.cpp"]
 
 HIPCC_FLAGS = [

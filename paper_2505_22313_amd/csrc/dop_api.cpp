@@ -261,17 +261,21 @@ dop_status launch_range(const dop_context *cctx, const KParams &kp, int first, i
   return DOP_OK;
 }
 
-// One wavelength of a three-pass path (rows, columns with H, rows); its
-// passes are timed as pass_a_fwd, pass_c and pass_a_inv.
+// A group (or one wavelength) of a three-pass path (rows, columns with H,
+// rows); its passes are timed as pass_a_fwd, pass_c (one per wavelength) and
+// pass_a_inv.
 static dop_status launch_three(const dop_context *cctx, const KParams &kp, hipStream_t stream,
                                bool timed) {
   dop_context *ctx = const_cast<dop_context *>(cctx);
   std::vector<hipEvent_t> ev;
-  dop_status s = take_events(ctx, 3, timed, &ev);
+  dop_status s = take_events(ctx, kp.group + 2, timed, &ev);
   if (s != DOP_OK) return s;
   hipEvent_t *evp = ev.empty() ? nullptr : ev.data();
   const hipError_t e = tri_path(kp) ? launch_tri(kp, stream, evp) : launch_small(kp, stream, evp);
-  keep_events(ctx, ev, {0, 2, 4});
+  std::vector<int> slot(kp.group + 2, 2);
+  slot.front() = 0;
+  slot.back() = 4;
+  keep_events(ctx, ev, std::move(slot));
   if (e != hipSuccess)
     return fail(DOP_ERR_DEVICE, "kernel launch failed: %s", hipGetErrorString(e));
   return DOP_OK;
@@ -295,7 +299,8 @@ int psf_group(const dop_problem *prob, const void *saved_u, size_t ws_bytes) {
   const bool small = small_path(plan_id(grid_cols(prob), grid_rows(prob)));
   if (saved_u && !small) return 1;
   const size_t field = workspace_bytes(prob);
-  const int g = plan_max_group(plan_id(grid_cols(prob), grid_rows(prob)));
+  const int plan = plan_id(grid_cols(prob), grid_rows(prob));
+  const int g = small ? small_max_group(plan) : plan_max_group(plan);
   const size_t fit = ws_bytes / field;
   int r = prob->n_lambda < g ? prob->n_lambda : g;
   if (fit < (size_t)r) r = (int)fit;
@@ -310,6 +315,13 @@ static bool profiling(const dop_context *cctx, bool timed) {
   return ctx->prof_on;
 }
 
+// The square grids of the small-grid path run one wavelength at a time while
+// passes are timed: their times are those of single wavelengths.
+static bool one_by_one(const dop_context *ctx, const dop_problem *prob, bool timed) {
+  const int plan = plan_id(grid_cols(prob), grid_rows(prob));
+  return plan <= kSmallMaxLM && profiling(ctx, timed);
+}
+
 dop_status enqueue_psf(const dop_context *ctx, const dop_problem *prob, const float *h,
                        const float *amp, float *psf, void *saved_u, void *ws, size_t ws_bytes,
                        hipStream_t stream, bool timed) {
@@ -322,7 +334,7 @@ dop_status enqueue_psf_range(const dop_context *ctx, const dop_problem *prob, in
                              size_t ws_bytes, hipStream_t stream, bool timed) {
   const size_t nn = (size_t)doe_rows(prob) * prob->n;
   int g = psf_group(prob, saved_u, ws_bytes);
-  if (small_path(plan_id(grid_cols(prob), grid_rows(prob))) && profiling(ctx, timed)) g = 1;
+  if (one_by_one(ctx, prob, timed)) g = 1;
   auto setup = [&](KParams &kp, int k, void *field) {
     fill_common(kp, ctx, prob, k, field);
     kp.in_mode = IN_PHASE;
@@ -419,6 +431,11 @@ dop_status dop_context_create(int device, dop_context **out) {
     for (int p = 1, l2 = 1 << (lm - 4); p <= 8; ++p)
       for (int j = 0; j < l2; ++j)
         host[tri_tw_offset(lm) + (p - 1) * l2 + j] = host[(p * j) << (kTwLog - lm)];
+  for (int l : kAxisLengths)
+    for (int j = 0; j < l; ++j) {
+      const double a = -2.0 * M_PI * (double)j / (double)l;
+      host[axis_tw_offset(l) + j] = make_float2((float)std::cos(a), (float)std::sin(a));
+    }
   dop_context *ctx = new dop_context();
   ctx->device = device;
   hipError_t e = hipMalloc(reinterpret_cast<void **>(&ctx->tw), sizeof(float2) * kTwTotal);
@@ -664,8 +681,8 @@ dop_status dop_psf_backward(dop_context *ctx, const dop_problem *prob, const flo
   // wavelengths per launch: as many as the workspace has fields for on the
   // small-grid path, else one
   int g = 1;
-  if (small_path(plan_id(grid_cols(prob), grid_rows(prob))) && !profiling(ctx, true))
-    while (g < kMaxGroup && g < prob->n_lambda &&
+  if (small_path(plan_id(grid_cols(prob), grid_rows(prob))) && !one_by_one(ctx, prob, true))
+    while (g < small_max_group(plan_id(grid_cols(prob), grid_rows(prob))) && g < prob->n_lambda &&
            workspace_bytes_op(prob, DOP_OP_PSF_BACKWARD, g + 1) <= ws_bytes)
       ++g;
   // with an upsampled design the passes accumulate the n x n fine gradient in

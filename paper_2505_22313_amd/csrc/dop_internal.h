@@ -19,7 +19,18 @@ constexpr int kTwN = 1 << kTwLog;
 constexpr int kTriMinLM = 12;
 constexpr int kTriMaxLM = 14;
 constexpr int tri_tw_offset(int lm) { return kTwN + (1 << (lm - 1)) - (1 << (kTriMinLM - 1)); }
-constexpr int kTwTotal = tri_tw_offset(kTriMaxLM + 1);
+// Then omega_L^i, i < L, of the axis lengths that are no power of two and
+// take the small-grid path, from axis_tw_offset(L).
+constexpr int kAxisLengths[] = {240, 720, 1440, 2144, 3600, 5360};
+constexpr int axis_tw_offset(int l) {
+  int at = tri_tw_offset(kTriMaxLM + 1);
+  for (int a : kAxisLengths) {
+    if (a == l) return at;
+    at += a;
+  }
+  return at;
+}
+constexpr int kTwTotal = axis_tw_offset(0);
 
 // Wavelengths per group: pass A forms, and pass A' accumulates, up to this
 // many fields (one workspace field each) per launch.
@@ -110,15 +121,19 @@ hipError_t launch_wavelength(const KParams &p, hipStream_t stream, hipEvent_t *e
 hipError_t launch_passes(const KParams &p, int first, int last, hipStream_t stream,
                          hipEvent_t *ev);
 
-// Small-grid path: square power-of-two grids of 2^kSmallMinLM .. 2^kSmallMaxLM
-// points per side run every operation as three passes: rows, columns with H,
-// rows.  small_path(plan) says whether a plan id is one of them; launch_small
-// enqueues the three passes of p.group wavelengths (PSF and gradient; 1 for
-// fields), with ev[0..3] (if not NULL) recorded before, between and after
-// them.
+// Small-grid path (small_grid.hip): square power-of-two grids of
+// 2^kSmallMinLM .. 2^kSmallMaxLM points per side, and the table grids whose
+// rows and columns fit a block, run every operation as three passes: rows,
+// columns with H, rows.  small_path(plan) says whether a plan id is one of
+// them, small_max_group(plan) how many wavelengths a launch takes at most;
+// launch_small enqueues the three passes of p.group wavelengths (PSF and
+// gradient; 1 for fields).  ev (if not NULL) gets p.group + 3 marks: before
+// the first pass, after it, after each field's column pass (launched one by
+// one then) and after the last pass.
 constexpr int kSmallMinLM = 4;
 constexpr int kSmallMaxLM = 11;
 bool small_path(int plan);
+int small_max_group(int plan);
 hipError_t launch_small(const KParams &p, hipStream_t stream, hipEvent_t *ev);
 
 // Three-pass path of a half-filled plane (three_pass.hip): tri_path(p) says
