@@ -191,8 +191,8 @@ void fill_common(KParams &kp, const dop_context *ctx, const dop_problem *prob, i
   const int mx = grid_cols(prob), my = grid_rows(prob);
   kp.n = prob->n;
   kp.plan = plan_id(mx, my);
-  if (kp.plan >= kTriMinLM && kp.plan <= kTriMaxLM) {
-    kp.tw3 = ctx->tw + tri_tw_offset(kp.plan);
+  if (tri_grid(kp.plan)) {
+    kp.tw3 = ctx->tw + (kp.plan <= kTriMaxLM ? tri_tw_offset(kp.plan) : kTri3600Tw);
     kp.pitch3 = tri_pitch(kp.plan, doe_rows(prob));
   }
   kp.nrows_in = doe_rows(prob);
@@ -436,6 +436,9 @@ dop_status dop_context_create(int device, dop_context **out) {
       const double a = -2.0 * M_PI * (double)j / (double)l;
       host[axis_tw_offset(l) + j] = make_float2((float)std::cos(a), (float)std::sin(a));
     }
+  for (int p = 1; p <= 8; ++p)
+    for (int j = 0; j < 3600 / 16; ++j)
+      host[kTri3600Tw + (p - 1) * (3600 / 16) + j] = host[axis_tw_offset(3600) + p * j];
   dop_context *ctx = new dop_context();
   ctx->device = device;
   hipError_t e = hipMalloc(reinterpret_cast<void **>(&ctx->tw), sizeof(float2) * kTwTotal);

@@ -30,7 +30,9 @@ constexpr int axis_tw_offset(int l) {
   }
   return at;
 }
-constexpr int kTwTotal = axis_tw_offset(0);
+// Last, the three-pass path's cross twiddles of 3600^2.
+constexpr int kTri3600Tw = axis_tw_offset(0);
+constexpr int kTwTotal = kTri3600Tw + 3600 / 2;
 
 // Wavelengths per group: pass A forms, and pass A' accumulates, up to this
 // many fields (one workspace field each) per launch.
@@ -142,6 +144,7 @@ hipError_t launch_small(const KParams &p, hipStream_t stream, hipEvent_t *ev);
 // wavelength in any input and output mode, with ev[0..3] (if not NULL)
 // recorded before, between and after its passes.  It needs the workspace of
 // one field.
+int tri_grid(int plan);  // points per side if the plan may take the path, else 0
 bool tri_path(const KParams &p);
 int tri_pitch(int plan, int nrows);
 hipError_t launch_tri(const KParams &p, hipStream_t s, hipEvent_t *ev);

@@ -1,6 +1,6 @@
 // Three-pass propagation of a zero-padded field on the square power-of-two
-// grids of 4096 .. 16384 points per side, where whole rows and columns fit in
-// one block:
+// grids of 4096 .. 16384 points per side and on 3600^2, where whole rows and
+// columns fit in one block:
 //   R : DFT along x of each DOE row (the input formed on the fly), written
 //       column by column;
 //   K : per column, DFT along y, times H (Eq. 3), inverse DFT along y;
@@ -40,27 +40,40 @@
 #include <type_traits>
 
 #include "asm_device.h"
+#include "asm_stages.h"
 #include "dop_internal.h"
 
 namespace dop {
 namespace {
 
+constexpr int kTri3600 = kTabBase + 4;  // 3600 = 16 * 15 * 15
+
+// LM: log2 M of a power of two, or the plan id of 3600^2.
 template <int LM>
 struct Tri {
-  static constexpr int M = 1 << LM;
+  static constexpr bool POW2 = LM < kTabBase;
+  static constexpr TablePlan TP = table_plan(POW2 ? -1 : LM - kTabBase);
+  static constexpr int M = POW2 ? 1 << LM : TP.ax * TP.bx;
   static constexpr int CR = 16;           // cross radix
   static constexpr int NP = CR / 2;       // frequency pairs p
-  static constexpr int L2 = M / CR;       // wave-local transform: 16 * RX * 16
-  static constexpr int RX = L2 / 256;     // its middle radix: 1 (none), 2, 4
-  static constexpr int IW = L2 / 16;      // lanes per pair of transforms
-  static constexpr int NW = 64 / IW;      // pairs of transforms per wavefront
-  static constexpr int ROWS = NW;         // rows per block of passes R and R'
-  static constexpr int TROW = 64 * NP;    // threads of passes R and R'
-  static constexpr int TCOL = L2;         // threads of pass K: a column pair
-  // LDS elements of one wavefront's 1024 points: one pad element per 16 keeps
-  // the first exchange (stride 16) free of bank conflicts
-  static constexpr int REG = 1024 + 64;
-  static constexpr int SUB = L2 + L2 / 16;  // of one pair of transforms
+  static constexpr int L2 = M / CR;       // wave-local transform: LP * RX * LP
+  static constexpr int LP = POW2 ? 16 : 15;           // points of it per lane
+  static constexpr int RX = L2 / (LP * LP);           // its middle radix: 1 (none), 2, 4
+  static constexpr int IW = L2 / LP;                  // lanes per pair of transforms
+  static constexpr int NW = 64 / IW;                  // pairs of transforms per wavefront
+  static constexpr int ROWS = NW;                     // rows per block of passes R and R'
+  static constexpr int TROW = 64 * NP;                // threads of passes R and R'
+  static constexpr int HALF = TROW / ROWS;            // from a thread's first item to its second
+  static constexpr int TCOL = 64 * 2 * NP / NW;       // threads of pass K: a column pair
+  // Lanes and items past the end (3600: four lanes of a wavefront, 28 threads
+  // of a row's items) repeat the last one, and store what it stores.
+  static constexpr bool EXACT = IW * NW == 64;
+  // LDS position of element pos: one pad element per 16 keeps the first
+  // exchange (stride 16) free of bank conflicts; stride 15 needs none
+  static constexpr int pad(int pos) { return POW2 ? pos + pos / 16 : pos; }
+  static constexpr int SUB = pad(L2);     // of one pair of transforms
+  static constexpr int REG = SUB * NW;    // of one wavefront's
+  static_assert(M == CR * L2 && L2 == LP * RX * LP && L2 == LP * IW, "transform");
   // Pairs interleaved in memory: passes R and R' touch runs of 16 QG ROWS
   // bytes, pass K 128 / QG bytes of each line.  Runs under 64 bytes cost the
   // row passes more than the split lines cost pass K (us per wavelength of
@@ -73,15 +86,17 @@ struct Tri {
 };
 
 // Twiddles of the wave-local transform, in LDS: omega_L2^(t i) at [t - 1][i],
-// i < IW, and omega_(16 RX)^(t k) at [t - 1][k], k < 16.
+// t < LP, i < IW, and omega_(16 RX)^(t k) at [t - 1][k], k < 16.
 template <int LM>
 struct LocalTw {
   using P = Tri<LM>;
-  float2 a[15 * P::IW];
+  float2 a[(P::LP - 1) * P::IW];
   float2 b[P::RX > 1 ? (P::RX - 1) * 16 : 1];
   DEV void fill(const float2 *__restrict__ tw, int threads) {
-    for (int i = threadIdx.x; i < 15 * P::IW; i += threads)
-      a[i] = tw[((i / P::IW + 1) * (i % P::IW)) << (kTwLog - LM + 4)];
+    for (int i = threadIdx.x; i < (P::LP - 1) * P::IW; i += threads) {
+      const int e = (i / P::IW + 1) * (i % P::IW);
+      a[i] = P::POW2 ? tw[e << (kTwLog - LM + 4)] : tw[axis_tw_offset(P::M) + e * P::CR];
+    }
     if constexpr (P::RX > 1)
       for (int i = threadIdx.x; i < (P::RX - 1) * 16; i += threads)
         b[i] = tw[((i / 16 + 1) * (i % 16)) << (kTwLog - 4 - (P::RX == 2 ? 1 : 2))];
@@ -106,22 +121,22 @@ DEV void sched_fence() { __builtin_amdgcn_sched_barrier(0); }
 // Exchange of 2 x 16 points inside a wavefront's LDS region, real parts then
 // imaginary parts (one 8-byte access moves a component of both transforms).
 // Register t goes to put[PS idx(t)], and is taken from get[GS t].
-template <int PS, int GS, class Idx>
+template <int LP, int PS, int GS, class Idx>
 DEV void wave_exchange(float2 (&a)[16], float2 (&b)[16], float2 *put, const float2 *get,
                        const Idx &idx) {
-  float2 re[16];
+  float2 re[LP];
   wave_sync();
 #pragma unroll
-  for (int t = 0; t < 16; ++t) put[PS * idx(t)] = make_float2(a[t].x, b[t].x);
+  for (int t = 0; t < LP; ++t) put[PS * idx(t)] = make_float2(a[t].x, b[t].x);
   wave_sync();
 #pragma unroll
-  for (int t = 0; t < 16; ++t) re[t] = get[GS * t];
+  for (int t = 0; t < LP; ++t) re[t] = get[GS * t];
   wave_sync();
 #pragma unroll
-  for (int t = 0; t < 16; ++t) put[PS * idx(t)] = make_float2(a[t].y, b[t].y);
+  for (int t = 0; t < LP; ++t) put[PS * idx(t)] = make_float2(a[t].y, b[t].y);
   wave_sync();
 #pragma unroll
-  for (int t = 0; t < 16; ++t) {
+  for (int t = 0; t < LP; ++t) {
     const float2 im = get[GS * t];
     a[t] = make_float2(re[t].x, im.x);
     b[t] = make_float2(re[t].y, im.y);
@@ -130,20 +145,20 @@ DEV void wave_exchange(float2 (&a)[16], float2 (&b)[16], float2 *put, const floa
 
 // L2-point DFTs of a (sign INV) and b (the opposite sign) over the IW lanes
 // `it` that share them.  In and out, register t of lane it holds element
-// it + IW t.  reg is the LDS element of position 0; position pos lies
-// (pos + pos / 16) S elements on.  Every access is one of three bases plus a
+// it + IW t, t < LP.  reg is the LDS element of position 0; position pos lies
+// pad(pos) S elements on.  Every access is one of three bases plus a
 // constant, so no address is kept per element.
 template <int LM, int S, bool INV>
 DEV void local_dft(float2 (&a)[16], float2 (&b)[16], float2 *reg, const int it,
                    const LocalTw<LM> &tw) {
   using P = Tri<LM>;
-  constexpr int IW = P::IW, RX = P::RX;
-  constexpr int NAT = (IW + IW / 16) * S;  // from element it + IW t to the next t
-  Dft<16, INV>::run(a);
+  constexpr int IW = P::IW, RX = P::RX, LP = P::LP;
+  constexpr int NAT = P::pad(IW) * S;  // from element it + IW t to the next t
+  Dft<LP, INV>::run(a);
   sched_fence();
-  Dft<16, !INV>::run(b);
-  float2 *nat = reg + (it + (it >> 4)) * S;
-  wave_exchange<S, NAT>(a, b, reg + 17 * it * S, nat, [](int t) { return t; });
+  Dft<LP, !INV>::run(b);
+  float2 *nat = reg + P::pad(it) * S;
+  wave_exchange<LP, S, NAT>(a, b, reg + P::pad(LP) * it * S, nat, [](int t) { return t; });
   if constexpr (RX > 1) {
     constexpr int NI = 16 / RX;  // radix-RX items per lane: it + IW i
     const int k = it & 15;
@@ -174,21 +189,21 @@ DEV void local_dft(float2 (&a)[16], float2 (&b)[16], float2 *reg, const int it,
       }
     }
     // output t of item i goes to (item - k) RX + k + 16 t
-    wave_exchange<17 * S, NAT>(a, b, reg + (17 * RX * (it >> 4) + k) * S, nat, [](int s) {
+    wave_exchange<LP, 17 * S, NAT>(a, b, reg + (17 * RX * (it >> 4) + k) * S, nat, [](int s) {
       const int i = s % NI, t = s / NI;
       return IW / 16 * RX * i + t;
     });
   }
 #pragma unroll
-  for (int t = 1; t < 16; ++t) {
+  for (int t = 1; t < LP; ++t) {
     const float2 w = tw.a[(t - 1) * IW + it];
     a[t] = INV ? cmulc(a[t], w) : cmul(a[t], w);
     b[t] = INV ? cmul(b[t], w) : cmulc(b[t], w);
     if (t % 4 == 3) sched_fence();
   }
-  Dft<16, INV>::run(a);
+  Dft<LP, INV>::run(a);
   sched_fence();
-  Dft<16, !INV>::run(b);
+  Dft<LP, !INV>::run(b);
 }
 
 // 16-point DFT whose inputs 8..15 are zero (forward): the zeros' butterflies
@@ -253,10 +268,10 @@ DEV void cross_twiddle(float2 (&v)[16], const float2 (&w)[8]) {
 // go out as (k1 = p, mirror) pairs, and each lane takes its wave-local
 // transform's.  Pair p of the first / second item is put0 / put1[PP p], the
 // lane's element t is get[GS t].
-template <int PP, int GS>
+template <int LP, int PP, int GS>
 DEV void cross_exchange_fwd(float2 (&v0)[16], float2 (&v1)[16], float2 *put0, float2 *put1,
                             const float2 *get) {
-  float2 re[16];
+  float2 re[LP];
 #pragma unroll
   for (int p = 0; p < 8; ++p) {
     put0[PP * p] = make_float2(v0[p].x, v0[mir(p)].x);
@@ -264,7 +279,7 @@ DEV void cross_exchange_fwd(float2 (&v0)[16], float2 (&v1)[16], float2 *put0, fl
   }
   __syncthreads();
 #pragma unroll
-  for (int t = 0; t < 16; ++t) re[t] = get[GS * t];
+  for (int t = 0; t < LP; ++t) re[t] = get[GS * t];
   __syncthreads();
 #pragma unroll
   for (int p = 0; p < 8; ++p) {
@@ -273,7 +288,7 @@ DEV void cross_exchange_fwd(float2 (&v0)[16], float2 (&v1)[16], float2 *put0, fl
   }
   __syncthreads();
 #pragma unroll
-  for (int t = 0; t < 16; ++t) {
+  for (int t = 0; t < LP; ++t) {
     const float2 im = get[GS * t];
     v0[t] = make_float2(re[t].x, im.x);
     v1[t] = make_float2(re[t].y, im.y);
@@ -283,13 +298,13 @@ DEV void cross_exchange_fwd(float2 (&v0)[16], float2 (&v1)[16], float2 *put0, fl
 // The way back: lanes hold their wave-local transform's values (v0: k1 = p,
 // v1: mirror) and take the 2 x 16 values of their two items.  The first
 // writes go to the wavefront's own region, which only it has read since.
-template <int PP, int GS>
+template <int LP, int PP, int GS>
 DEV void cross_exchange_inv(float2 (&v0)[16], float2 (&v1)[16], float2 *put, const float2 *get0,
                             const float2 *get1) {
   float2 r0[8], r1[8];
   wave_sync();
 #pragma unroll
-  for (int t = 0; t < 16; ++t) put[GS * t] = make_float2(v0[t].x, v1[t].x);
+  for (int t = 0; t < LP; ++t) put[GS * t] = make_float2(v0[t].x, v1[t].x);
   __syncthreads();
 #pragma unroll
   for (int p = 0; p < 8; ++p) {
@@ -298,7 +313,7 @@ DEV void cross_exchange_inv(float2 (&v0)[16], float2 (&v1)[16], float2 *put, con
   }
   __syncthreads();
 #pragma unroll
-  for (int t = 0; t < 16; ++t) put[GS * t] = make_float2(v0[t].y, v1[t].y);
+  for (int t = 0; t < LP; ++t) put[GS * t] = make_float2(v0[t].y, v1[t].y);
   __syncthreads();
 #pragma unroll
   for (int p = 0; p < 8; ++p) {
@@ -324,25 +339,27 @@ DEV int fresh(int v) {
 template <int LM>
 struct RowGeo {
   using P = Tri<LM>;
-  // item threads: row r, items j and j + L2 / 2
-  int r, j;
+  // item threads: row r, items j and j2; whether the second is this thread's own
+  int r, j, j2;
+  bool own2;
   // transform lanes: pair p, row rw, lane `it` of the transform
   int p, rw, it;
   DEV explicit RowGeo(int tid) {
     r = tid % P::ROWS;
     j = tid / P::ROWS;
+    own2 = P::EXACT || j + P::HALF < P::L2;
+    j2 = own2 ? j + P::HALF : P::L2 - 1;
     p = tid >> 6;
     rw = (tid & 63) % P::ROWS;
     it = (tid & 63) / P::ROWS;
+    if (!P::EXACT) it = it < P::IW ? it : P::IW - 1;
   }
-  // LDS element of the first item in pair 0 (the second lies ITEM2 on, pair p
-  // REG p), of this lane's transform, and of its element 0 (NAT from one
-  // element to the next)
-  static constexpr int ITEM2 = (P::L2 / 2 + P::L2 / 32) * P::ROWS;
-  static constexpr int NAT = (P::IW + P::IW / 16) * P::ROWS;
-  DEV int item() const { return (j + (j >> 4)) * P::ROWS + r; }
+  // LDS element of an item in pair 0 (pair p lies REG p on), of this lane's
+  // transform, and of its element 0 (NAT from one element to the next)
+  static constexpr int NAT = P::pad(P::IW) * P::ROWS;
+  DEV int item(int i) const { return P::pad(i) * P::ROWS + r; }
   DEV int region() const { return p * P::REG + rw; }
-  DEV int natural() const { return region() + (it + (it >> 4)) * P::ROWS; }
+  DEV int natural() const { return region() + P::pad(it) * P::ROWS; }
 };
 
 // ---------------------------------------------------------------------------
@@ -383,7 +400,7 @@ TRI_KERNEL(Tri<LM>::TROW) void k_tri_rows_fwd(KParams p) {
 #pragma unroll
     for (int t = 0; t < 8; ++t) {
       v0[t] = load(g.j + L2 * t);
-      v1[t] = load(g.j + L2 / 2 + L2 * t);
+      v1[t] = load(g.j2 + L2 * t);
     }
   }
   tw.fill(p.tw, T);
@@ -399,18 +416,18 @@ TRI_KERNEL(Tri<LM>::TROW) void k_tri_rows_fwd(KParams p) {
     load_cross<LM>(w, p.tw3, g.j);
     dft16_half_in(v0);
     cross_twiddle<false>(v0, w);
-    load_cross<LM>(w, p.tw3, g.j + L2 / 2);
+    load_cross<LM>(w, p.tw3, g.j2);
     dft16_half_in(v1);
     cross_twiddle<false>(v1, w);
   }
-  cross_exchange_fwd<P::REG, G::NAT>(v0, v1, lds + g.item(), lds + g.item() + G::ITEM2,
-                                     lds + g.natural());
+  cross_exchange_fwd<P::LP, P::REG, G::NAT>(v0, v1, lds + g.item(g.j), lds + g.item(g.j2),
+                                            lds + g.natural());
   local_dft<LM, P::ROWS, false>(v0, v1, lds + g.region(), g.it, tw);
   const int y = y0 + g.rw;
   if (y < p.nrows_in) {
     f4v *out = reinterpret_cast<f4v *>(p.ws) + y * P::QG;
 #pragma unroll
-    for (int t = 0; t < 16; ++t)
+    for (int t = 0; t < P::LP; ++t)
       out[P::pair_item(g.p * L2 + g.it + IW * t, p.pitch3)] = f4v{v0[t].x, v0[t].y, v1[t].x, v1[t].y};
   }
 }
@@ -428,7 +445,7 @@ TRI_KERNEL(Tri<LM>::TCOL) void k_tri_cols(KParams p) {
   f4v *col = reinterpret_cast<f4v *>(p.ws) + P::pair_item(q, p.pitch3);
   float2 v0[16], v1[16];  // item j of the cross stage in the two columns
   {
-    const int j = threadIdx.x;
+    const int j = P::EXACT ? threadIdx.x : min((int)threadIdx.x, L2 - 1);
 #pragma unroll
     for (int t = 0; t < 8; ++t) {
       const int y = j + L2 * t;
@@ -452,14 +469,19 @@ TRI_KERNEL(Tri<LM>::TCOL) void k_tri_cols(KParams p) {
   struct Place {
     int it, unit;
     float2 *item, *reg, *nat;  // column 0's pair 0, the unit's region, element 0
-    DEV Place(float2 *lds, int tid)
-        : it(tid % IW), unit((tid >> 6) * P::NW + (tid & 63) / IW), item(lds + tid + (tid >> 4)),
-          reg(lds + unit * P::SUB), nat(reg + it + (it >> 4)) {}
+    DEV Place(float2 *lds, int tid) {
+      const int lane = P::EXACT ? tid & 63 : min(tid & 63, IW * P::NW - 1);
+      it = lane % IW;
+      unit = (tid >> 6) * P::NW + lane / IW;
+      item = lds + P::pad(P::EXACT ? tid : min(tid, L2 - 1));
+      reg = lds + unit * P::SUB;
+      nat = reg + P::pad(it);
+    }
   };
-  constexpr int NAT = IW + IW / 16, PP = 2 * P::SUB;
+  constexpr int NAT = P::pad(IW), PP = 2 * P::SUB, LP = P::LP;
   {
     const Place at(lds, fresh(threadIdx.x));
-    cross_exchange_fwd<PP, NAT>(v0, v1, at.item, at.item + P::SUB, at.nat);
+    cross_exchange_fwd<LP, PP, NAT>(v0, v1, at.item, at.item + P::SUB, at.nat);
     local_dft<LM, 1, false>(v0, v1, at.reg, at.it, tw);
   }
   {
@@ -475,7 +497,7 @@ TRI_KERNEL(Tri<LM>::TCOL) void k_tri_cols(KParams p) {
     if (pk) {
       const int ky0 = pk + CR * it;
 #pragma unroll
-      for (int t = 0; t < 16; ++t) {
+      for (int t = 0; t < LP; ++t) {
         const float2 hv = h(fresh(ky0) + CR * IW * t);  // H(-ky) = H(ky)
         v0[t] = cmul(v0[t], hv);
         v1[t] = cmul(v1[t], hv);
@@ -483,7 +505,7 @@ TRI_KERNEL(Tri<LM>::TCOL) void k_tri_cols(KParams p) {
       }
     } else {
 #pragma unroll
-      for (int t = 0; t < 16; ++t) {
+      for (int t = 0; t < LP; ++t) {
         const int ky = fresh(CR * it) + CR * IW * t;
         v0[t] = cmul(v0[t], h(ky));
         sched_fence();
@@ -495,9 +517,9 @@ TRI_KERNEL(Tri<LM>::TCOL) void k_tri_cols(KParams p) {
   {
     const Place at(lds, fresh(threadIdx.x));
     local_dft<LM, 1, true>(v0, v1, at.reg, at.it, tw);
-    cross_exchange_inv<PP, NAT>(v0, v1, at.nat, at.item, at.item + P::SUB);
+    cross_exchange_inv<LP, PP, NAT>(v0, v1, at.nat, at.item, at.item + P::SUB);
   }
-  const int j = fresh(threadIdx.x);
+  const int j = P::EXACT ? fresh(threadIdx.x) : min(fresh(threadIdx.x), L2 - 1);
   {
     float2 w[8];
     load_cross<LM>(w, p.tw3, j);
@@ -540,7 +562,7 @@ TRI_KERNEL(Tri<LM>::TROW) void k_tri_rows_inv(KParams p) {
     const int y = y0 + g.rw;
     const f4v *in = reinterpret_cast<const f4v *>(p.ws) + (y < p.nrows_out ? y : 0) * P::QG;
 #pragma unroll
-    for (int t = 0; t < 16; ++t) {
+    for (int t = 0; t < P::LP; ++t) {
       const f4v x = in[P::pair_item(g.p * L2 + g.it + IW * t, p.pitch3)];
       v0[t] = make_float2(x.x, x.y);
       v1[t] = make_float2(x.z, x.w);
@@ -549,8 +571,8 @@ TRI_KERNEL(Tri<LM>::TROW) void k_tri_rows_inv(KParams p) {
   tw.fill(p.tw, T);
   __syncthreads();
   local_dft<LM, P::ROWS, true>(v0, v1, lds + g.region(), g.it, tw);
-  cross_exchange_inv<P::REG, G::NAT>(v0, v1, lds + g.natural(), lds + g.item(),
-                                     lds + g.item() + G::ITEM2);
+  cross_exchange_inv<P::LP, P::REG, G::NAT>(v0, v1, lds + g.natural(), lds + g.item(g.j),
+                                            lds + g.item(g.j2));
   const int y = y0 + g.r;
   const bool live = y < p.nrows_out;
   const size_t row = (size_t)(live ? y : 0) * n;
@@ -561,25 +583,29 @@ TRI_KERNEL(Tri<LM>::TROW) void k_tri_rows_inv(KParams p) {
     sched_fence();
     idft16_half_out(v0);
     sched_fence();
-    load_cross<LM>(w, p.tw3, g.j + L2 / 2);
+    load_cross<LM>(w, p.tw3, g.j2);
     cross_twiddle<true>(v1, w);
     sched_fence();
     idft16_half_out(v1);
   }
   if (!live) return;
-  // Item 2 t + i of this thread is column j + L2 / 2 (2 t + i).  Straight-line
+  // Value 2 t + i of this thread is column t of its item i.  Straight-line
   // loads, then straight-line stores: one branch on a DOE that fills the half
-  // plane, where no column has to be masked.
-  const int j = fresh(g.j);
+  // plane, where no column has to be masked.  (A repeated item is left out:
+  // its sums would be added to twice.)
+  const int j = fresh(g.j), j2 = fresh(g.j2);
+  const bool own2 = g.own2;
+  auto col = [&](int t) { return (t % 2 ? j2 : j) + L2 * (t / 2); };
   auto emit = [&](auto whole) {
     constexpr bool WHOLE = decltype(whole)::value;
+    auto wanted = [&](int t) { return (WHOLE || col(t) < n) && (P::EXACT || t % 2 == 0 || own2); };
     auto value = [&](int t) { return t % 2 ? v1[t / 2] : v0[t / 2]; };
     float acc[16] = {};
     if (OUTM != OUT_FIELD && !p.first) {
       const float *sum = (OUTM == OUT_PSF ? p.psf : p.grad_h) + row;
 #pragma unroll
       for (int t = 0; t < 16; ++t) {
-        const int x = j + L2 / 2 * t;
+        const int x = col(t);
         acc[t] = sum[WHOLE || x < n ? x : 0];
       }
     }
@@ -588,7 +614,7 @@ TRI_KERNEL(Tri<LM>::TROW) void k_tri_rows_inv(KParams p) {
       const float *arow = p.amp ? p.amp + row : nullptr;
 #pragma unroll
       for (int t = 0; t < 16; ++t) {
-        const int x = j + L2 / 2 * t, xc = WHOLE || x < n ? x : 0;
+        const int x = col(t), xc = WHOLE || x < n ? x : 0;
         float2 e = doe_phase(hrow[xc >> p.up_log2], p.phase_turns);
         if (arow) e = cscale(e, arow[xc]);
         const float2 w = value(t);
@@ -602,8 +628,8 @@ TRI_KERNEL(Tri<LM>::TROW) void k_tri_rows_inv(KParams p) {
       float *out = (OUTM == OUT_PSF ? p.psf : p.grad_h) + row;
 #pragma unroll
       for (int t = 0; t < 16; ++t) {
-        const int x = j + L2 / 2 * t;
-        if (WHOLE || x < n) out[x] = acc[t];
+        const int x = col(t);
+        if (wanted(t)) out[x] = acc[t];
       }
     }
     float2 *field = OUTM == OUT_FIELD ? p.u_out : OUTM == OUT_PSF ? p.saved_out : nullptr;
@@ -611,8 +637,8 @@ TRI_KERNEL(Tri<LM>::TROW) void k_tri_rows_inv(KParams p) {
       field += row;
 #pragma unroll
       for (int t = 0; t < 16; ++t) {
-        const int x = j + L2 / 2 * t;
-        if (WHOLE || x < n) field[x] = cscale(value(t), p.inv_m2);
+        const int x = col(t);
+        if (wanted(t)) field[x] = cscale(value(t), p.inv_m2);
       }
     }
   };
@@ -651,15 +677,20 @@ hipError_t launch_lm(const KParams &p, hipStream_t s, hipEvent_t *ev) {
 
 }  // namespace
 
+// The grids of the path by plan id; 0: none.
+int tri_grid(int plan) {
+  return plan >= kTriMinLM && plan <= kTriMaxLM ? 1 << plan : plan == kTri3600 ? 3600 : 0;
+}
+static_assert(Tri<kTri3600>::M == 3600, "the table's 3600^2 grid");
+
 bool tri_path(const KParams &p) {
-  if (p.plan < kTriMinLM || p.plan > kTriMaxLM || p.full) return false;
-  const int half = 1 << (p.plan - 1);
-  return p.n <= half && p.nrows_in <= half && p.nrows_out <= half;
+  const int half = tri_grid(p.plan) / 2;
+  return half && !p.full && p.n <= half && p.nrows_in <= half && p.nrows_out <= half;
 }
 
 // Items of QG pairs' rows, rounded up to an odd number of 128-byte lines.
 int tri_pitch(int plan, int nrows) {
-  const int qg = plan == 14 ? Tri<14>::QG : plan == 13 ? Tri<13>::QG : Tri<12>::QG;
+  const int qg = plan == 14 ? Tri<14>::QG : plan == 13 ? Tri<13>::QG : 1;
   return ((nrows * qg + 7) / 8 | 1) * 8;
 }
 
@@ -668,6 +699,7 @@ hipError_t launch_tri(const KParams &p, hipStream_t s, hipEvent_t *ev) {
     case 12: return launch_lm<12>(p, s, ev);
     case 13: return launch_lm<13>(p, s, ev);
     case 14: return launch_lm<14>(p, s, ev);
+    case kTri3600: return launch_lm<kTri3600>(p, s, ev);
     default: return hipErrorInvalidValue;
   }
 }

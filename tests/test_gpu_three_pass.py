@@ -1,8 +1,8 @@
 """The three-pass path of a half-filled plane (square power-of-two grids of
-4096 .. 16384, DOE at most half of each axis, DOE window wanted) against the
-five digit passes: the same DOE placed in the corner of one that is a row and
-a column larger than half the grid, with a zero aperture outside, takes the
-five passes, and propagation does not depend on the placement.  PSF, saved
+4096 .. 16384 and 3600^2, DOE at most half of each axis, DOE window wanted)
+against the passes other DOEs take: the same DOE placed in the corner of one that is a row and
+a column larger than half the grid, with a zero aperture outside, takes
+those, and propagation does not depend on the placement.  PSF, saved
 fields, gradient and propagated field, at the edges of the tiles: DOEs that
 fill the half plane, one row or column short of it, odd ones, a single point.
 One ragged problem per option is also compared with the FP64 oracle.
@@ -54,8 +54,9 @@ def check(got, want, l2_tol, elem_tol, what):
     (4096, 2048, 2048), (4096, 2047, 2048), (4096, 2048, 2047), (4096, 1, 1), (4096, 3, 1025),
     (4096, 1501, 257), (8192, 4096, 4096), (8192, 4095, 4093), (8192, 5, 4096),
     (16384, 8192, 8192), (16384, 8191, 8189), (16384, 9, 700),
+    (3600, 1800, 1800), (3600, 1799, 1797), (3600, 1, 1800), (3600, 901, 3),
 ])
-def test_three_pass_equals_five(api, m, ny, nx):
+def test_three_pass_equals_the_general_path(api, m, ny, nx):
     gen = torch.Generator(device="cuda").manual_seed(m + ny + nx)
     lams = np.array([0.45, 0.62])
     w = np.array([0.7, 1.3], dtype=np.float32)
