@@ -52,6 +52,7 @@ class Problem:
             raise ValueError("out_mode must be 'crop' or 'full'")
         self.out_mode = out_mode
         self.bandlimit = bool(bandlimit)
+        self._ws_bytes = {}  # workspace_size's results: op -> (extents, bytes)
         self._c = DopProblem()
         c = self._c
         c.n, c.m, c.dx, c.z = self.nx, self.mx, self.dx, self.z
@@ -98,8 +99,16 @@ class Problem:
 
 
 def workspace_size(prob, op=L.DOP_OP_PSF):
+    # the size follows from the extents alone, so it is asked for again only
+    # when they have changed (each call checks the whole problem by itself)
+    c = prob._c
+    key = (c.n, c.m, c.ny, c.my, c.upsample)
+    known = prob._ws_bytes.get(op)
+    if known is not None and known[0] == key:
+        return known[1]
     out = ctypes.c_size_t(0)
     check(lib().dop_workspace_size(None, prob.ptr(), op, ctypes.byref(out)), "dop_workspace_size")
+    prob._ws_bytes[op] = (key, out.value)
     return out.value
 
 
@@ -176,11 +185,20 @@ def default_context(device=None):
     return ctx
 
 
+# the current stream's handle, without the stream object around it
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream_handle(device):
+    if _raw_stream is not None:
+        return _raw_stream(device)
     return torch.cuda.current_stream(device).cuda_stream
 
 
 def _need(t, name, dtype, shape, device):
+    if (isinstance(t, torch.Tensor) and t.dtype is dtype and t.is_cuda
+            and t.get_device() == device and t.shape == shape and t.is_contiguous()):
+        return t
     if not isinstance(t, torch.Tensor):
         raise TypeError(f"{name} must be a torch tensor")
     if t.dtype != dtype:
@@ -195,7 +213,7 @@ def _need(t, name, dtype, shape, device):
 
 
 def _ptr(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
 def propagate(u_in, prob, k=0, ctx=None, out=None):
@@ -211,7 +229,7 @@ def propagate(u_in, prob, k=0, ctx=None, out=None):
     nbytes = workspace_size(prob, L.DOP_OP_PROPAGATE)
     ws = ctx.workspace(nbytes, stream)
     check(lib().dop_propagate(ctx.handle, prob.ptr(), int(k), _ptr(u_in), _ptr(out), _ptr(ws),
-                              ws.numel(), ctypes.c_void_p(stream)), "dop_propagate")
+                              ws.numel(), stream), "dop_propagate")
     return out
 
 
@@ -270,7 +288,7 @@ def psf(h, prob, amp=None, save_fields=False, ctx=None, out=None, group=4):
     stream = _stream_handle(dev)
     ws, nbytes = _psf_workspace(ctx, prob, stream, save_fields, group)
     check(lib().dop_psf(ctx.handle, prob.ptr(), _ptr(h), _ptr(amp), _ptr(out), _ptr(saved),
-                        _ptr(ws), nbytes, ctypes.c_void_p(stream)), "dop_psf")
+                        _ptr(ws), nbytes, stream), "dop_psf")
     return (out, saved) if save_fields else out
 
 
@@ -290,7 +308,7 @@ def psf_noalloc(h, prob, amp=None, out=None, saved=None, ctx=None):
     if saved is not None:
         _need(saved, "saved", torch.complex64, (prob.k,) + prob.doe_shape, dev)
     check(lib().dop_psf_noalloc(ctx.handle, prob.ptr(), _ptr(h), _ptr(amp), _ptr(out), _ptr(saved),
-                                ctypes.c_void_p(_stream_handle(dev))), "dop_psf_noalloc")
+                                _stream_handle(dev)), "dop_psf_noalloc")
     return out
 
 
@@ -315,7 +333,7 @@ def psf_backward(h, prob, saved_u, grad_psf, amp=None, ctx=None, out=None):
     ws, _ = _grouped_workspace(ctx, stream, nbytes + (256 if g > 1 else 0), field, g)
     check(lib().dop_psf_backward(ctx.handle, prob.ptr(), _ptr(h), _ptr(amp), _ptr(saved_u),
                                  _ptr(grad_psf), _ptr(out), _ptr(ws), ws.numel(),
-                                 ctypes.c_void_p(stream)), "dop_psf_backward")
+                                 stream), "dop_psf_backward")
     return out
 
 
@@ -357,7 +375,7 @@ def probe_bandwidth(kind, buf, nbytes=None, m=0, ctx=None):
     moved = ctypes.c_size_t(0)
     check(lib().dop_probe_bandwidth(ctx.handle, PROBE_KINDS[kind], _ptr(buf), nbytes, int(m),
                                     ctypes.byref(moved),
-                                    ctypes.c_void_p(_stream_handle(ctx.device))),
+                                    _stream_handle(ctx.device)),
           "dop_probe_bandwidth")
     return moved.value
 
@@ -379,7 +397,7 @@ def upsample(coarse, s, kind="nearest", ctx=None, out=None):
         out = torch.empty(fine, dtype=torch.float32, device=coarse.device)
     _need(out, "out", torch.float32, fine, dev)
     check(lib().dop_upsample_rect(ctx.handle, UPSAMPLE_KINDS[kind], ncy, ncx, int(s),
-                                  _ptr(coarse), _ptr(out), ctypes.c_void_p(_stream_handle(dev))),
+                                  _ptr(coarse), _ptr(out), _stream_handle(dev)),
           "dop_upsample_rect")
     return out
 
@@ -400,7 +418,7 @@ def upsample_adjoint(grad_fine, s, kind="nearest", ctx=None, out=None):
     _need(out, "out", torch.float32, (ncy, ncx), dev)
     check(lib().dop_upsample_adjoint_rect(ctx.handle, UPSAMPLE_KINDS[kind], ncy, ncx, int(s),
                                           _ptr(grad_fine), _ptr(out),
-                                          ctypes.c_void_p(_stream_handle(dev))),
+                                          _stream_handle(dev)),
           "dop_upsample_adjoint_rect")
     return out
 

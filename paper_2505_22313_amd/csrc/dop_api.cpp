@@ -272,10 +272,12 @@ static dop_status launch_three(const dop_context *cctx, const KParams &kp, hipSt
   if (s != DOP_OK) return s;
   hipEvent_t *evp = ev.empty() ? nullptr : ev.data();
   const hipError_t e = tri_path(kp) ? launch_tri(kp, stream, evp) : launch_small(kp, stream, evp);
-  std::vector<int> slot(kp.group + 2, 2);
-  slot.front() = 0;
-  slot.back() = 4;
-  keep_events(ctx, ev, std::move(slot));
+  if (evp) {
+    std::vector<int> slot(kp.group + 2, 2);
+    slot.front() = 0;
+    slot.back() = 4;
+    keep_events(ctx, ev, std::move(slot));
+  }
   if (e != hipSuccess)
     return fail(DOP_ERR_DEVICE, "kernel launch failed: %s", hipGetErrorString(e));
   return DOP_OK;
