@@ -442,6 +442,12 @@ struct TablePlan {
 };
 constexpr int kTabBase = 100;
 constexpr int kNumTab = 14;
+// 16080 x 10720: 16 x 16 B tiles fill a quarter of a wavefront's lanes, and a
+// 1005-row C tile (153 KB) leaves one block per CU.  With 120 x 134 rows the B
+// tiles hold 1920 points, and 32 columns give the 67-point stage of C 64
+// items, a whole wavefront per share, in a 34 KB tile: per wavelength B 789 ->
+// 428, B' 726 -> 425, C 1530 -> 1016 us (A and A' 441 and 511 -> 527 and 590
+// beside the faster C).
 __host__ __device__ constexpr TablePlan table_plan(int i) {
   return i == 0    ? TablePlan{15, 16, 15, 16}        // 240^2
          : i == 1  ? TablePlan{45, 16, 45, 16}        // 720^2
@@ -455,7 +461,7 @@ __host__ __device__ constexpr TablePlan table_plan(int i) {
          : i == 9  ? TablePlan{128, 16, 16, 32}       // 512 x 2048
          : i == 10 ? TablePlan{134, 16, 15, 16}       // 240 x 2144
          : i == 11 ? TablePlan{15, 16, 16, 335}       // 5360 x 240
-         : i == 12 ? TablePlan{670, 16, 16, 1005}     // 16080 x 10720
+         : i == 12 ? TablePlan{670, 16, 120, 134, 32, 256}  // 16080 x 10720
          : i == 13 ? TablePlan{670, 128, 128, 1005, 8, 512}  // 128640 x 85760: 2^7 3 5 67 x 2^8 5 67
                    : TablePlan{0, 0, 0, 0};
 }
