@@ -213,6 +213,10 @@ DOP_KERNEL(Plan<PID>::TA) void k_pass_a_fwd(KParams p) {
   // (h, amp) for IN_PHASE, the field for IN_FIELD, the saved field for
   // IN_GRAD; columns x >= n are zero.
   float2 pre[FS::PER][FS::R];
+  constexpr bool GRAD = INM == IN_GRAD;
+  // dL/dPSF beside the saved field (read where it is used it stalled each
+  // tile: 65536^2 7.07 -> 6.02 ms, 28800^2 1.89 -> 1.49 ms, 16384^2 557 -> 400 us)
+  float gpre[GRAD ? FS::PER : 1][GRAD ? FS::R : 1];
   // A tile is one input row: its arrays are addressed as a tile-uniform row
   // base plus a 32-bit byte offset per element.
   auto fetch = [&](int tile, int tid) {
@@ -222,6 +226,7 @@ DOP_KERNEL(Plan<PID>::TA) void k_pass_a_fwd(KParams p) {
     const float *arow = p.amp ? p.amp + rowin : nullptr;
     const float2 *frow = INM == IN_FIELD ? p.u_in + rowin : INM == IN_GRAD ? p.saved_in + rowin
                                                                           : nullptr;
+    const float *grow = GRAD ? p.gpsf + rowin : nullptr;
     const int xb0 = (tile % RUNS) * RA;
 #pragma unroll
     for (int i = 0; i < FS::PER; ++i) {
@@ -240,6 +245,7 @@ DOP_KERNEL(Plan<PID>::TA) void k_pass_a_fwd(KParams p) {
                               arow ? *at_byte(arow, ux * 4u) : 1.f);
             else v = *at_byte(frow, ux * 8u);
           }
+          if constexpr (GRAD) gpre[i][t] = x < n ? *at_byte(grow, (unsigned)x * 4u) : 0.f;
           pre[i][t] = v;
         }
       }
@@ -284,8 +290,7 @@ DOP_KERNEL(Plan<PID>::TA) void k_pass_a_fwd(KParams p) {
             } else if constexpr (INM == IN_FIELD) {
               v[i][t] = r;
             } else {
-              const int x = BX * (j + t * FS::LR) + xb0 + b;
-              v[i][t] = x < n ? cscale(r, p.two_wk * p.gpsf[(size_t)y * n + x]) : r;
+              v[i][t] = cscale(r, p.two_wk * gpre[i][t]);  // r = 0 past column n
             }
           }
         }
@@ -595,6 +600,12 @@ DOP_KERNEL(Plan<PID>::TA) void k_pass_a_inv(KParams p) {
   constexpr int LRL = AX / LS::R;
   using SSL = StageShape<G, LS::R>;
   constexpr int APER = VIA_FN ? 1 : LS::PER, AR = VIA_FN ? 1 : LS::R;
+  // Whether the gradient's output stage reads its heights (and aperture) in
+  // batches ahead of the stores: 16384^2 grid 522 -> 408 us, 28800^2 2.31 ->
+  // 2.02 ms, 40000^2 3.36 -> 3.06 ms.  The 512- and 1024-thread tiles of the
+  // larger powers of two have no registers left for a batch (92 bytes of
+  // spills: 65536^2 7.4 -> 10.7 ms).
+  constexpr bool GRAD_BATCH = OUTM == OUT_GRADH && !VIA_FN && !(P::POW2 && T >= 512);
   __shared__ float2 lds[AX * RA];
   __shared__ TwLds<PID> tw;
   tw_fill<PID, T>(tw, p.tw);
@@ -755,6 +766,49 @@ DOP_KERNEL(Plan<PID>::TA) void k_pass_a_inv(KParams p) {
         dft_tile_hooked<G, true, false, SRC_REG, SNK_REG, P::THI>(lds, tw.hi, NoLoad{}, NoStore{},
                                                                  hook, v, u, tid);
         const bool last = q + 1 == ngroup;
+        if constexpr (GRAD_BATCH) {
+          // the output stage's own reads come ahead of the stores, which the
+          // compiler must assume to alias them, in batches that the registers
+          // beside the prefetch hold
+          constexpr int NB = 8;
+          __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+          for (int i = 0; i < LS::PER; ++i) {
+            const int it = loop_tid() + i * T;
+            int j = 0, b = 0;
+            if (SSL::EXACT || it < SSL::ITEMS) decode_item<G, LS::R>(it, j, b);
+#pragma unroll
+            for (int t0 = 0; t0 < LS::R; t0 += NB) {
+              float hv[NB], av[NB];
+#pragma unroll
+              for (int t = t0; t < t0 + NB && t < LS::R; ++t) {
+                unsigned c;
+                if (!out_col(xb0, j + t * LRL, b, c)) c = 0;
+                hv[t - t0] = orow.h[c >> p.up_log2];
+                av[t - t0] = orow.amp ? *at_byte(orow.amp, c * 4u) : 1.f;
+              }
+#pragma unroll
+              for (int t = t0; t < t0 + NB && t < LS::R; ++t) {
+                const float2 e = cscale(doe_phase(hv[t - t0], p.phase_turns), av[t - t0]);
+                acc[i][t] = grad_add(acc[i][t], p.ck_m2, u[i][t], e);
+              }
+              __builtin_amdgcn_sched_barrier(0);
+            }
+          }
+#pragma unroll
+          for (int i = 0; i < LS::PER; ++i) {
+            const int it = loop_tid() + i * T;
+            if (SSL::EXACT || it < SSL::ITEMS) {
+              int j, b;
+              decode_item<G, LS::R>(it, j, b);
+#pragma unroll
+              for (int t = 0; t < LS::R; ++t) {
+                unsigned c;
+                if (out_col(xb0, j + t * LRL, b, c)) *at_byte(orow.acc, c * 4u) = acc[i][t];
+              }
+            }
+          }
+        } else {
 #pragma unroll
         for (int i = 0; i < LS::PER; ++i) {
           const int it = tid + i * T;
@@ -769,6 +823,7 @@ DOP_KERNEL(Plan<PID>::TA) void k_pass_a_inv(KParams p) {
               else acc[i][t] = psf_add(acc[i][t], wk, u[i][t]);
             }
           }
+        }
         }
       }
     }
