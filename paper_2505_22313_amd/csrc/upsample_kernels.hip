@@ -190,9 +190,10 @@ constexpr int kUpCols = 4;
 constexpr int kUpSpan = 64 * kUpCols;  // fine columns per block
 constexpr int kUpMaxSeg = 4;           // segments per wavefront
 
-// NEAR (V4 and s >= 3): a thread's columns start at one of two neighbouring
-// taps, so seven samples serve them all.
-template <bool V4, bool NEAR>
+// NEAR > 0 (V4 only): the first taps of a thread's four columns lie within
+// NEAR samples of each other (1 for s >= 3, 2 for s = 2, 3 for s = 1), so 6 +
+// NEAR samples serve them all.
+template <bool V4, int NEAR>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k_up_lanczos(int ncy, int ncx, int s, int nseg,
                                                     const float *__restrict__ in,
                                                     float *__restrict__ out) {
@@ -236,17 +237,26 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
       const float v = src[min(max(x, 0), ncx - 1)];
       return x >= 0 && x < ncx ? v : 0.f;
     };
-    float near[7];
-    if constexpr (NEAR) {
+    float near[6 + NEAR];
+    if constexpr (NEAR > 0) {
 #pragma unroll
-      for (int t = 0; t < 7; ++t) near[t] = sample(cx[0] + t);
+      for (int t = 0; t < 6 + NEAR; ++t) near[t] = sample(cx[0] + t);
     }
+    auto tap = [&](int c, int t) {
+      if constexpr (NEAR == 0) {
+        return sample(cx[c] + t);
+      } else {
+        float v = near[t];
+#pragma unroll
+        for (int d = 1; d <= NEAR; ++d) v = cx[c] == cx[0] + d ? near[t + d] : v;
+        return v;
+      }
+    };
 #pragma unroll
     for (int c = 0; c < kUpCols; ++c) {
       float a = 0.f;
 #pragma unroll
-      for (int t = 0; t < 6; ++t)
-        a += cw[c][t] * (!NEAR ? sample(cx[c] + t) : cx[c] == cx[0] ? near[t] : near[t + 1]);
+      for (int t = 0; t < 6; ++t) a += cw[c][t] * tap(c, t);
       o[c] = live ? a : 0.f;
     }
   };
@@ -438,9 +448,10 @@ hipError_t launch_upsample(int kind, int ncy, int ncx, int s, const float *coars
     while (nseg > 1 && (long long)cdiv(nfx, kUpSpan) * cdiv(ncy + 2, 4 * nseg) < 1024) nseg /= 2;
     const dim3 grid(cdiv(nfx, kUpSpan), cdiv(ncy + 2, 4 * nseg));
     const bool v4 = nfx % 4 == 0 && aligned16(fine);
-    const auto kernel = v4 && s >= 3 ? k_up_lanczos<true, true>
-                        : v4         ? k_up_lanczos<true, false>
-                                     : k_up_lanczos<false, false>;
+    const auto kernel = !v4      ? k_up_lanczos<false, 0>
+                        : s >= 3 ? k_up_lanczos<true, 1>
+                        : s == 2 ? k_up_lanczos<true, 2>
+                                 : k_up_lanczos<true, 3>;
     hipLaunchKernelGGL(kernel, grid, dim3(256), 0, stream, ncy, ncx, s, nseg, coarse, fine);
   }
   return hipGetLastError();
