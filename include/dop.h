@@ -142,7 +142,8 @@ const char *dop_last_error(void);
 /*
  * Create a context on HIP device `device`: uploads the twiddle table
  * (exp(-2 pi i j / 131072), generated in FP64 and rounded to c64, 1 MiB),
- * followed by re-ordered copies of its entries for some grids (112 KiB).
+ * followed by re-ordered copies for some grids and tables of axis lengths that
+ * are no power of two (about 230 KiB).
  * The context owns only that table.  Synchronous.
  */
 dop_status dop_context_create(int device, dop_context **out);
@@ -184,12 +185,13 @@ dop_status dop_psf(dop_context *ctx, const dop_problem *prob, const float *h,
  * consecutive wavelengths per group: the first pass forms the group's fields
  * from one read of h, and the last pass adds their intensities to the PSF in
  * one read-modify-write.  The result is bitwise the same as one wavelength
- * at a time.  Square power-of-two grids up to 2048 group in every call,
- * dop_psf_backward among them (its workspace then holds g fields before the
- * fine-grid gradient), except while dop_profile_enable times their passes;
- * other grids when saved_u is NULL.  Grids whose x digit has the factor 67
- * run one wavelength at a time, as do the 4096 .. 16384 grids where they take
- * three passes. */
+ * at a time.  Square power-of-two grids up to 2048, 240^2, 720^2, 1440^2,
+ * 720 x 240, 512 x 2048 and 5360 x 240 group in every call, dop_psf_backward
+ * among them (its workspace then holds g fields before the fine-grid
+ * gradient; square powers of two not while dop_profile_enable times their
+ * passes); other grids when saved_u is NULL.  Grids whose x digit has the
+ * factor 67 run one wavelength at a time, as do 3600^2 and the 4096 .. 16384
+ * grids where they take three passes. */
 
 /*
  * dop_psf for callers that cannot allocate device memory (code under HIP
