@@ -336,6 +336,7 @@ def ceilings_measure(api, torch, ws, m, stream_bytes=16 << 30):
     copy, in-place read+write) and pass C's access pattern without its
     arithmetic on the m x m field.  GB/s of bytes moved, HIP-event timed."""
     out = {}
+    stream_bytes = min(stream_bytes, ws.numel() // 128 * 128)  # a smaller workload's workspace
     for kind in ("read", "write", "copy", "inplace"):
         moved = api.probe_bandwidth(kind, ws, stream_bytes)
         ms = _event_ms(torch, lambda: api.probe_bandwidth(kind, ws, stream_bytes), 5)

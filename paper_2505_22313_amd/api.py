@@ -234,7 +234,7 @@ def propagate(u_in, prob, k=0, ctx=None, out=None):
 
 
 # Fields up to this size are grouped without asking how much memory is free
-# (four of them are a 65th of the card's): the grids up to 2048 x 2048 run
+# (four of them are a thousandth of the card's memory): small grids run
 # several wavelengths per launch given the fields.
 _SMALL_FIELD = 64 << 20
 
