@@ -978,6 +978,7 @@ hipError_t launch_passes(const KParams &p, int first, int last, hipStream_t s, h
     case 16: return launch_range<16>(p, first, last, s, ev);
     case 17: return launch_range<17>(p, first, last, s, ev);
     case kTabBase + 3: return launch_range<kTabBase + 3>(p, first, last, s, ev);
+    case kTab3600: return launch_range<kTab3600>(p, first, last, s, ev);
     case kTabBase + 5: return launch_range<kTabBase + 5>(p, first, last, s, ev);
     case kTabBase + 6: return launch_range<kTabBase + 6>(p, first, last, s, ev);
     case kTabBase + 12: return launch_range<kTabBase + 12>(p, first, last, s, ev);

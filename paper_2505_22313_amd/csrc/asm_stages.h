@@ -442,6 +442,7 @@ struct TablePlan {
 };
 constexpr int kTabBase = 100;
 constexpr int kNumTab = 14;
+constexpr int kTab3600 = kTabBase + 4;  // 3600^2, the grid all three paths share
 // 28800^2: C tiles have 240 and 256 items a stage, so 256 threads (two more
 // blocks per CU than with 512): 3.08 -> 2.80 ms per wavelength, 4.8 TB/s.
 // 16080 x 10720: 16 x 16 B tiles fill a quarter of a wavefront's lanes, and a

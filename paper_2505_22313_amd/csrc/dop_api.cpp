@@ -183,14 +183,33 @@ static void set_group_entry(KParams &g, int q, const KParams &one) {
   g.ck_m2_g[q] = one.ck_m2;
 }
 
-// Fill the per-wavelength kernel parameters shared by every operation.
-void fill_common(KParams &kp, const dop_context *ctx, const dop_problem *prob, int k, void *ws) {
+static bool full_plane(const dop_problem *prob) { return prob->out_mode == DOP_OUT_FULL; }
+
+// The passes of an operation (by its input mode) on `prob`: they follow from
+// the problem alone, not from the workspace or the wavelengths of one call, so
+// that a result is the same bits however its wavelengths are grouped.
+Route route_of(const dop_problem *prob, InMode in) {
+  const int plan = plan_id(grid_cols(prob), grid_rows(prob)), ny = doe_rows(prob);
+  if (tri_path(plan, prob->n, ny, full_plane(prob))) return ROUTE_TRI;
+  const int rows = ny + (full_plane(prob) ? grid_rows(prob) : ny);
+  return small_path(plan, in, rows, in == IN_FIELD ? 1 : prob->n_lambda) ? ROUTE_SMALL : ROUTE_FIVE;
+}
+
+// Fill the kernel parameters of wavelength k that follow from the problem and
+// the operation (its input mode).
+void fill_common(KParams &kp, const dop_context *ctx, const dop_problem *prob, int k, void *ws,
+                 InMode in) {
   std::memset(&kp, 0, sizeof(kp));
   kp.ws = static_cast<float2 *>(ws);
   kp.tw = ctx->tw;
   const int mx = grid_cols(prob), my = grid_rows(prob);
   kp.n = prob->n;
   kp.plan = plan_id(mx, my);
+  kp.route = route_of(prob, in);
+  kp.in_mode = in;
+  kp.out_mode = in == IN_PHASE ? OUT_PSF : in == IN_FIELD ? OUT_FIELD : OUT_GRADH;
+  kp.full = full_plane(prob);
+  kp.nrows_out = kp.full ? my : doe_rows(prob);
   if (tri_grid(kp.plan)) {
     kp.tw3 = ctx->tw + (kp.plan <= kTriMaxLM ? tri_tw_offset(kp.plan) : kTri3600Tw);
     kp.pitch3 = tri_pitch(kp.plan, doe_rows(prob));
@@ -271,7 +290,8 @@ static dop_status launch_three(const dop_context *cctx, const KParams &kp, hipSt
   dop_status s = take_events(ctx, kp.group + 2, timed, &ev);
   if (s != DOP_OK) return s;
   hipEvent_t *evp = ev.empty() ? nullptr : ev.data();
-  const hipError_t e = tri_path(kp) ? launch_tri(kp, stream, evp) : launch_small(kp, stream, evp);
+  const hipError_t e =
+      kp.route == ROUTE_TRI ? launch_tri(kp, stream, evp) : launch_small(kp, stream, evp);
   if (evp) {
     std::vector<int> slot(kp.group + 2, 2);
     slot.front() = 0;
@@ -284,7 +304,7 @@ static dop_status launch_three(const dop_context *cctx, const KParams &kp, hipSt
 }
 
 dop_status launch(const dop_context *ctx, const KParams &kp, hipStream_t stream) {
-  if (small_path(kp.plan) || tri_path(kp)) return launch_three(ctx, kp, stream, true);
+  if (kp.route != ROUTE_FIVE) return launch_three(ctx, kp, stream, true);
   return launch_range(ctx, kp, 0, kNumPasses - 1, stream);
 }
 
@@ -298,7 +318,7 @@ dop_status check_ctx_device(const dop_context *ctx) {
 }
 
 int psf_group(const dop_problem *prob, const void *saved_u, size_t ws_bytes) {
-  const bool small = small_path(plan_id(grid_cols(prob), grid_rows(prob)));
+  const bool small = route_of(prob, IN_PHASE) == ROUTE_SMALL;
   if (saved_u && !small) return 1;
   const size_t field = workspace_bytes(prob);
   const int plan = plan_id(grid_cols(prob), grid_rows(prob));
@@ -338,11 +358,7 @@ dop_status enqueue_psf_range(const dop_context *ctx, const dop_problem *prob, in
   int g = psf_group(prob, saved_u, ws_bytes);
   if (one_by_one(ctx, prob, timed)) g = 1;
   auto setup = [&](KParams &kp, int k, void *field) {
-    fill_common(kp, ctx, prob, k, field);
-    kp.in_mode = IN_PHASE;
-    kp.out_mode = OUT_PSF;
-    kp.full = prob->out_mode == DOP_OUT_FULL;
-    kp.nrows_out = kp.full ? grid_rows(prob) : doe_rows(prob);
+    fill_common(kp, ctx, prob, k, field, IN_PHASE);
     kp.h = h;
     kp.amp = amp;
     kp.psf = psf;
@@ -353,14 +369,14 @@ dop_status enqueue_psf_range(const dop_context *ctx, const dop_problem *prob, in
     setup(kp, k0, ws);
     kp.first = (k0 == 0);
     kp.saved_out = saved_u ? static_cast<float2 *>(saved_u) + (size_t)k0 * nn : nullptr;
-    if (tri_path(kp)) gk = 1;
+    if (kp.route == ROUTE_TRI) gk = 1;
     kp.group = gk;
     for (int q = 1; q < gk; ++q) {
       KParams kq;
-      fill_common(kq, ctx, prob, k0 + q, ws);
+      fill_common(kq, ctx, prob, k0 + q, ws, IN_PHASE);
       set_group_entry(kp, q, kq);
     }
-    if (small_path(kp.plan) || tri_path(kp)) {
+    if (kp.route != ROUTE_FIVE) {
       const dop_status s = launch_three(ctx, kp, stream, timed);
       if (s != DOP_OK) return s;
     } else if (gk == 1) {
@@ -605,11 +621,7 @@ dop_status dop_propagate(dop_context *ctx, const dop_problem *prob, int k, const
   if ((s = check_ws(prob, DOP_OP_PROPAGATE, ws, ws_bytes)) != DOP_OK) return s;
   if ((s = check_ctx_device(ctx)) != DOP_OK) return s;
   KParams kp;
-  fill_common(kp, ctx, prob, k, ws);
-  kp.in_mode = IN_FIELD;
-  kp.out_mode = OUT_FIELD;
-  kp.full = prob->out_mode == DOP_OUT_FULL;
-  kp.nrows_out = kp.full ? grid_rows(prob) : doe_rows(prob);
+  fill_common(kp, ctx, prob, k, ws, IN_FIELD);
   kp.first = 1;
   kp.u_in = static_cast<const float2 *>(u_in);
   kp.u_out = static_cast<float2 *>(u_out);
@@ -686,7 +698,7 @@ dop_status dop_psf_backward(dop_context *ctx, const dop_problem *prob, const flo
   // wavelengths per launch: as many as the workspace has fields for on the
   // small-grid path, else one
   int g = 1;
-  if (small_path(plan_id(grid_cols(prob), grid_rows(prob))) && !one_by_one(ctx, prob, true))
+  if (route_of(prob, IN_GRAD) == ROUTE_SMALL && !one_by_one(ctx, prob, true))
     while (g < small_max_group(plan_id(grid_cols(prob), grid_rows(prob))) && g < prob->n_lambda &&
            workspace_bytes_op(prob, DOP_OP_PSF_BACKWARD, g + 1) <= ws_bytes)
       ++g;
@@ -696,18 +708,14 @@ dop_status dop_psf_backward(dop_context *ctx, const dop_problem *prob, const flo
       up > 1 ? reinterpret_cast<float *>(static_cast<char *>(ws) + fine_grad_offset(prob, g)) : grad_h;
   for (int k = 0; k < prob->n_lambda; k += g) {
     KParams kp;
-    fill_common(kp, ctx, prob, k, ws);
+    fill_common(kp, ctx, prob, k, ws, IN_GRAD);
     kp.group = prob->n_lambda - k < g ? prob->n_lambda - k : g;
     for (int q = 1; q < kp.group; ++q) {
       KParams kq;
-      fill_common(kq, ctx, prob, k + q, ws);
+      fill_common(kq, ctx, prob, k + q, ws, IN_GRAD);
       kq.zl = -kq.zl;
       set_group_entry(kp, q, kq);
     }
-    kp.in_mode = IN_GRAD;
-    kp.out_mode = OUT_GRADH;
-    kp.full = 0;
-    kp.nrows_out = doe_rows(prob);
     kp.first = (k == 0);
     kp.adjoint = 1;
     kp.zl = -kp.zl;  // conj(H) = H at -z (the band limit depends on |z| only)

@@ -6,6 +6,8 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include "../../include/dop.h"
+
 namespace dop {
 
 // Size of the shared twiddle table: W[j] = exp(-2 pi i j / kTwN).
@@ -57,7 +59,11 @@ enum OutMode : int {
   OUT_GRADH = 2   // grad_h (+)= c_k Im(g_E conj(E_k))
 };
 
-// Everything one wavelength's five passes need.  Passed by value.
+// The passes an operation takes: the five digit passes of asm_kernels.hip, or
+// three passes over whole rows and columns (small_grid.hip, three_pass.hip).
+enum Route : int { ROUTE_FIVE = 0, ROUTE_SMALL = 1, ROUTE_TRI = 2 };
+
+// Everything one wavelength's passes need.  Passed by value.
 struct KParams {
   float2 *ws;            // My x Mx c64 workspace (row pitch Mx + kRowPad)
   const float2 *tw;      // twiddle table, kTwN entries
@@ -65,6 +71,7 @@ struct KParams {
   int pitch3;            // items from one group of column pairs to the next (three-pass path)
   int n;                 // DOE columns Nx (row length of every N-wide array)
   int plan;              // plan id of the grid (plan_id)
+  int route;             // Route of the operation
   int nrows_in;          // rows of the padded input that may be nonzero
   int nrows_out;         // rows of the output plane that are needed
   int p0x, p0y;          // (Mx - Nx) / 2, (My - Ny) / 2
@@ -113,6 +120,9 @@ struct KParams {
 
 constexpr int kNumPasses = 5;
 
+// Route of an operation (by its input mode) on a valid problem (dop_api.cpp).
+Route route_of(const dop_problem *prob, InMode in);
+
 // Enqueue the five passes of one wavelength on `stream`.  If `ev` is not
 // NULL, ev[0..5] are recorded before the first pass, between passes and
 // after the last one.
@@ -125,27 +135,30 @@ hipError_t launch_passes(const KParams &p, int first, int last, hipStream_t stre
 
 // Small-grid path (small_grid.hip): square power-of-two grids of
 // 2^kSmallMinLM .. 2^kSmallMaxLM points per side, and the table grids whose
-// rows and columns fit a block, run every operation as three passes: rows,
-// columns with H, rows.  small_path(plan) says whether a plan id is one of
-// them, small_max_group(plan) how many wavelengths a launch takes at most;
+// rows and columns fit a block, run an operation as three passes: rows,
+// columns with H, rows.  small_path says whether an operation takes them, from
+// its plan id, its input mode, the rows of its first and last pass together
+// and its wavelengths (1 for fields); small_max_group(plan) says how many
+// wavelengths a launch takes at most;
 // launch_small enqueues the three passes of p.group wavelengths (PSF and
 // gradient; 1 for fields).  ev (if not NULL) gets p.group + 3 marks: before
 // the first pass, after it, after each field's column pass (launched one by
 // one then) and after the last pass.
 constexpr int kSmallMinLM = 4;
 constexpr int kSmallMaxLM = 11;
-bool small_path(int plan);
+bool small_path(int plan, InMode in, int rows, int n_lambda);
 int small_max_group(int plan);
 hipError_t launch_small(const KParams &p, hipStream_t stream, hipEvent_t *ev);
 
-// Three-pass path of a half-filled plane (three_pass.hip): tri_path(p) says
-// whether the problem set up in p (plan, extents, window) takes it; tri_pitch
+// Three-pass path of a half-filled plane (three_pass.hip): tri_path says
+// whether a problem takes it, from its plan id, DOE (n columns, rows rows) and
+// window; tri_pitch
 // gives KParams::pitch3 for a number of rows; launch_tri enqueues one
 // wavelength in any input and output mode, with ev[0..3] (if not NULL)
 // recorded before, between and after its passes.  It needs the workspace of
 // one field.
 int tri_grid(int plan);  // points per side if the plan may take the path, else 0
-bool tri_path(const KParams &p);
+bool tri_path(int plan, int n, int rows, bool full);
 int tri_pitch(int plan, int nrows);
 hipError_t launch_tri(const KParams &p, hipStream_t s, hipEvent_t *ev);
 

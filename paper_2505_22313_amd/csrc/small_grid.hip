@@ -33,8 +33,9 @@ namespace dop {
 // PSF of one and of four wavelengths, gradient step of one (us per call), five
 // passes -> three: 240^2 25, 137, 55 -> 17, 22, 38; 720^2 30, 140, 65 -> 24,
 // 41, 47; 1440^2 56, 172, 112 -> 40, 88, 81; 2144^2 149, 618, 306 -> 112,
-// 457, 229; 3600^2 210, 799, 439 -> 178, 732, 367; 512 x 2048 33, 135, 68 ->
-// 29, 58, 57; 5360 x 240 60, 198, 120 -> 52, 105, 105.  3072^2 was no faster
+// 457, 229; 512 x 2048 33, 135, 68 ->
+// 29, 58, 57; 5360 x 240 60, 198, 120 -> 52, 105, 105.  3600^2 takes them for
+// some operations (small_path).  3072^2 was no faster
 // (118, 443, 240 against 120, 491, 247: one 123 KB column tile per CU) and
 // keeps the five passes, as do the grids whose columns do not fit.
 struct SmallTab {
@@ -46,7 +47,7 @@ __host__ __device__ constexpr SmallTab small_tab(int i) {
   return i == 0    ? SmallTab{4, 64, 4, 64, true}       // 240^2
          : i == 1  ? SmallTab{2, 128, 4, 192, true}     // 720^2
          : i == 2  ? SmallTab{1, 192, 4, 768, true}     // 1440^2
-         : i == 4  ? SmallTab{1, 256, 3, 768, false}    // 3600^2
+         : i == kTab3600 - kTabBase ? SmallTab{1, 256, 3, 768, false}
          : i == 7  ? SmallTab{1, 320, 4, 512, false}    // 2144^2
          : i == 8  ? SmallTab{4, 64, 4, 192, true}      // 720 x 240
          : i == 9  ? SmallTab{1, 128, 4, 256, true}     // 512 x 2048
@@ -403,9 +404,17 @@ static hipError_t launch_small_plan(const KParams &p, hipStream_t s, hipEvent_t 
   return hipGetLastError();
 }
 
-bool small_path(int plan) {
-  return plan < kTabBase ? plan >= kSmallMinLM && plan <= kSmallMaxLM
-                         : small_tab(plan - kTabBase).c > 0;
+// 3600^2: these passes cost more per row than the five, and run one wavelength
+// at a time where the five group them.  us per wavelength, five passes -> three,
+// by the rows of the first and last pass together: one wavelength 3960 rows 217
+// -> 185, 5400 233 -> 221, 6480 240 -> 248, 6840 245 -> 258; four wavelengths
+// 3960 rows 211 -> 209, 5400 225 -> 245, 6480 232 -> 266, 6840 237 -> 282; a
+// field 3960 rows 209 -> 186, 5400 222 -> 221, 6480 233 -> 247, 6840 240 -> 262.
+// The gradient gains at every size (6480 rows 334 -> 298).
+bool small_path(int plan, InMode in, int rows, int n_lambda) {
+  if (plan < kTabBase) return plan >= kSmallMinLM && plan <= kSmallMaxLM;
+  if (plan == kTab3600 && in != IN_GRAD) return rows <= (n_lambda == 1 ? 5400 : 4000);
+  return small_tab(plan - kTabBase).c > 0;
 }
 
 int small_max_group(int plan) {
@@ -425,7 +434,7 @@ hipError_t launch_small(const KParams &p, hipStream_t s, hipEvent_t *ev) {
     case kTabBase + 0: return launch_small_plan<kTabBase + 0>(p, s, ev);
     case kTabBase + 1: return launch_small_plan<kTabBase + 1>(p, s, ev);
     case kTabBase + 2: return launch_small_plan<kTabBase + 2>(p, s, ev);
-    case kTabBase + 4: return launch_small_plan<kTabBase + 4>(p, s, ev);
+    case kTab3600: return launch_small_plan<kTab3600>(p, s, ev);
     case kTabBase + 7: return launch_small_plan<kTabBase + 7>(p, s, ev);
     case kTabBase + 8: return launch_small_plan<kTabBase + 8>(p, s, ev);
     case kTabBase + 9: return launch_small_plan<kTabBase + 9>(p, s, ev);

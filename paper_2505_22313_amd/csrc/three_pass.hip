@@ -46,9 +46,7 @@
 namespace dop {
 namespace {
 
-constexpr int kTri3600 = kTabBase + 4;  // 3600 = 16 * 15 * 15
-
-// LM: log2 M of a power of two, or the plan id of 3600^2.
+// LM: log2 M of a power of two, or the plan id of 3600^2 (3600 = 16 * 15 * 15).
 template <int LM>
 struct Tri {
   static constexpr bool POW2 = LM < kTabBase;
@@ -679,13 +677,13 @@ hipError_t launch_lm(const KParams &p, hipStream_t s, hipEvent_t *ev) {
 
 // The grids of the path by plan id; 0: none.
 int tri_grid(int plan) {
-  return plan >= kTriMinLM && plan <= kTriMaxLM ? 1 << plan : plan == kTri3600 ? 3600 : 0;
+  return plan >= kTriMinLM && plan <= kTriMaxLM ? 1 << plan : plan == kTab3600 ? 3600 : 0;
 }
-static_assert(Tri<kTri3600>::M == 3600, "the table's 3600^2 grid");
+static_assert(Tri<kTab3600>::M == 3600, "the table's 3600^2 grid");
 
-bool tri_path(const KParams &p) {
-  const int half = tri_grid(p.plan) / 2;
-  return half && !p.full && p.n <= half && p.nrows_in <= half && p.nrows_out <= half;
+bool tri_path(int plan, int n, int rows, bool full) {
+  const int half = tri_grid(plan) / 2;
+  return half && !full && n <= half && rows <= half;
 }
 
 // Items of QG pairs' rows, rounded up to an odd number of 128-byte lines.
@@ -699,7 +697,7 @@ hipError_t launch_tri(const KParams &p, hipStream_t s, hipEvent_t *ev) {
     case 12: return launch_lm<12>(p, s, ev);
     case 13: return launch_lm<13>(p, s, ev);
     case 14: return launch_lm<14>(p, s, ev);
-    case kTri3600: return launch_lm<kTri3600>(p, s, ev);
+    case kTab3600: return launch_lm<kTab3600>(p, s, ev);
     default: return hipErrorInvalidValue;
   }
 }
