@@ -293,8 +293,10 @@ __global__ __launch_bounds__(SmallPlan<PID>::TR * GR) void k_small_rows_inv(KPar
 // C * 8 bytes wide, so 128 / (C * 8) neighbouring tiles share each cache
 // line: tiles go to blocks in the XCD-aware order, which puts neighbours on
 // one XCD and its L2 (at 1024^2 this took the pass from 18.7 to 14.1 us).
-// q0 + blockIdx.y: wavelength of the group.
-template <int PID>
+// q0 + blockIdx.y: wavelength of the group.  GR = 1: a single wavelength, whose
+// constants are the plain fields (choosing them by q ahead of the first loads
+// took 0.4 of 7 us at 512^2).
+template <int PID, int GR>
 __global__ __launch_bounds__(SmallPlan<PID>::TC) void k_small_cols(KParams p, int q0) {
   using S = SmallPlan<PID>;
   constexpr int MX = S::MX, M = S::MY, C = S::C, SJ = S::SJ, T = S::TC;
@@ -304,10 +306,11 @@ __global__ __launch_bounds__(SmallPlan<PID>::TC) void k_small_cols(KParams p, in
   __shared__ float2 tw[M];
   __shared__ double a2col[C];
   constexpr int NT = MX / C;
-  const int q = q0 + blockIdx.y;
-  float2 *const ws = p.ws + q * p.field_elems;
-  const double lam = group_value(p.lam_g, q), zl = group_value(p.zl_g, q);
-  const double flim_x = group_value(p.flim_x_g, q), flim_y = group_value(p.flim_y_g, q);
+  const int q = GR == 1 ? 0 : q0 + blockIdx.y;
+  float2 *const ws = GR == 1 ? p.ws : p.ws + q * p.field_elems;
+  const double lam = pick<GR>(p.lam, p.lam_g, q), zl = pick<GR>(p.zl, p.zl_g, q);
+  const double flim_x = pick<GR>(p.flim_x, p.flim_x_g, q);
+  const double flim_y = pick<GR>(p.flim_y, p.flim_y_g, q);
   auto gather = [&](int tile, float2 (&pre)[FS::PER][FS::R], int tid) {
     const int x0 = xcd_tile(tile, NT) * C;
     // rows at or past nrows_in are zero: read row 0 and replace (branch-free)
@@ -374,6 +377,19 @@ static void launch_rows_inv(const KParams &p, dim3 grid, hipStream_t s) {
   hipLaunchKernelGGL((k_small_rows_inv<PID, OUTM, 1>), grid, dim3(S::TR), 0, s, p);
 }
 
+// The column pass of `count` wavelengths of the group, from the q0-th on.
+template <int PID>
+static void launch_cols(const KParams &p, unsigned gc, int q0, int count, hipStream_t s) {
+  using S = SmallPlan<PID>;
+  if constexpr (S::GROUP) {
+    if (p.group > 1) {
+      hipLaunchKernelGGL((k_small_cols<PID, kMaxGroup>), dim3(gc, count), dim3(S::TC), 0, s, p, q0);
+      return;
+    }
+  }
+  hipLaunchKernelGGL((k_small_cols<PID, 1>), dim3(gc), dim3(S::TC), 0, s, p, 0);
+}
+
 template <int PID>
 static hipError_t launch_small_plan(const KParams &p, hipStream_t s, hipEvent_t *ev) {
   using S = SmallPlan<PID>;
@@ -390,10 +406,10 @@ static hipError_t launch_small_plan(const KParams &p, hipStream_t s, hipEvent_t 
   mark(ev, 1, s);
   const unsigned gc = grid(S::MX / S::C);
   if (!ev) {
-    hipLaunchKernelGGL(k_small_cols<PID>, dim3(gc, p.group), dim3(S::TC), 0, s, p, 0);
+    launch_cols<PID>(p, gc, 0, p.group, s);
   } else {  // a group's fields one launch each, so that each is timed
     for (int q = 0; q < p.group; ++q) {
-      hipLaunchKernelGGL(k_small_cols<PID>, dim3(gc), dim3(S::TC), 0, s, p, q);
+      launch_cols<PID>(p, gc, q, 1, s);
       mark(ev, q + 2, s);
     }
   }
