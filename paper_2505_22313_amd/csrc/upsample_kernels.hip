@@ -31,14 +31,6 @@ namespace {
 
 constexpr int kUpMaxS = 16;
 
-// Orders one wavefront's LDS accesses: LDS serves a wavefront in program
-// order, so only the compiler has to be held back.
-DEV void wave_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 // Lanczos-3 kernel L(x) = sinc(x) sinc(x/3), |x| < 3.
 DEV double lanczos3(double x) {
   const double ax = fabs(x);
@@ -179,32 +171,38 @@ DEV int seg_lo(int b, int s) { return s * (b + 2) + s / 2; }
 // LDS, its four wavefronts taking rows in turn; then each wavefront walks down
 // nseg segments of s fine rows that share their six coarse rows, the window of
 // six in registers, so that a fine sample costs six multiply-adds.  A thread
-// owns kUpCols fine columns (adjacent and stored as one 16-byte vector where
+// owns COLS fine columns: four (adjacent and stored as one 16-byte vector where
 // every fine row starts on a 16-byte boundary, V4; else 64 apart, so that a
-// wavefront stores whole lines).  The segment count is picked by the launcher
-// so that small maps still fill the chip.  2048^2, s = 8 (1.09 GB): 647 ->
-// 220 us, of the 215 that plain stores take; a tile in LDS spent its time on
-// two LDS reads per product and on FP64 taps per 4096 samples.
+// wavefront stores whole lines), or one.  The launcher picks the columns and
+// the segment count so that small and narrow maps still fill the chip.
+// 2048^2, s = 8 (1.09 GB): 647 -> 220 us, of the 215 that plain stores take; a
+// tile in LDS spent its time on two LDS reads per product and on FP64 taps per
+// 4096 samples.  The taps of all the block's rows are formed at its start:
+// formed per segment, they kept s = 1 at 510 us on 8192^2 (now 289).
 // ---------------------------------------------------------------------------
-constexpr int kUpCols = 4;
-constexpr int kUpSpan = 64 * kUpCols;  // fine columns per block
-constexpr int kUpMaxSeg = 4;           // segments per wavefront
+constexpr int kUpRows = 256;  // fine rows per block, at most: one row's taps per thread
+// segments per wavefront, at most, where a thread owns `cols` columns
+__host__ __device__ constexpr int up_max_seg(int cols, int s) {
+  return cols == 4 ? 4 : 64 / s < 16 ? 64 / s : 16;
+}
 
 // NEAR > 0 (V4 only): the first taps of a thread's four columns lie within
 // NEAR samples of each other (1 for s >= 3, 2 for s = 2, 3 for s = 1), so 6 +
 // NEAR samples serve them all.
-template <bool V4, int NEAR>
+template <bool V4, int NEAR, int COLS = 4>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k_up_lanczos(int ncy, int ncx, int s, int nseg,
                                                     const float *__restrict__ in,
                                                     float *__restrict__ out) {
   const int nfy = ncy * s, nfx = ncx * s;
+  constexpr int SPAN = 64 * COLS;  // fine columns per block
   __shared__ TapTable tt;
-  // taps of the block's fine columns, and of each wavefront's current segment
-  __shared__ float cws[6][kUpSpan];
-  __shared__ int cxs[kUpSpan];
-  __shared__ __align__(16) float rws[4][kUpMaxS][8];
+  // taps of the block's fine rows
+  __shared__ __align__(16) float rws[kUpRows][8];
   // coarse rows interpolated along x, from the block's first on; [lane][column]
-  __shared__ __align__(16) float hs[4 * kUpMaxSeg + 5][kUpSpan];
+  // (before them, the taps of the block's fine columns)
+  __shared__ __align__(16) float hs[4 * up_max_seg(COLS, 1) + 5][SPAN];
+  float (*const cws)[SPAN] = hs;
+  int *const cxs = reinterpret_cast<int *>(hs[6]);
   tap_table_fill(tt, s);
   // segments -3 .. ncy - 2 cover the fine rows
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
@@ -212,25 +210,34 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
   const int b1 = min(b0 + nseg, ncy - 1);
   {
     float w[6];
-    cxs[threadIdx.x] =
-        lanczos_taps(min((int)(blockIdx.x * kUpSpan + threadIdx.x), nfx - 1), s, ncx, tt, w);
+    if (threadIdx.x < SPAN) {
+      cxs[threadIdx.x] =
+          lanczos_taps(min((int)(blockIdx.x * SPAN + threadIdx.x), nfx - 1), s, ncx, tt, w);
 #pragma unroll
-    for (int t = 0; t < 6; ++t) cws[t][threadIdx.x] = w[t];
+      for (int t = 0; t < 6; ++t) cws[t][threadIdx.x] = w[t];
+    }
+    const int e = threadIdx.x, j = seg_lo(bb, s) + e;
+    if (e < 4 * nseg * s && j >= 0 && j < nfy) {
+      lanczos_taps(j, s, ncy, tt, w);
+#pragma unroll
+      for (int t = 0; t < 6; ++t) rws[e][t] = w[t];
+    }
   }
   __syncthreads();
   auto col = [&](int c) { return V4 ? 4 * lane + c : lane + 64 * c; };
-  const int x0 = blockIdx.x * kUpSpan;
-  int cx[kUpCols];
-  float cw[kUpCols][6];
+  const int x0 = blockIdx.x * SPAN;
+  int cx[COLS];
+  float cw[COLS][6];
 #pragma unroll
-  for (int c = 0; c < kUpCols; ++c) {
+  for (int c = 0; c < COLS; ++c) {
     cx[c] = cxs[col(c)];
 #pragma unroll
     for (int t = 0; t < 6; ++t) cw[c][t] = cws[t][col(c)];
   }
+  __syncthreads();  // the column taps have been read
   // coarse row `row` interpolated at this thread's columns (taps outside the
   // grid have weight zero and their samples count as zero)
-  auto interp = [&](int row, float (&o)[kUpCols]) {
+  auto interp = [&](int row, float (&o)[COLS]) {
     const float *src = in + (size_t)min(max(row, 0), ncy - 1) * ncx;
     const bool live = row >= 0 && row < ncy;
     auto sample = [&](int x) {
@@ -245,6 +252,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
     auto tap = [&](int c, int t) {
       if constexpr (NEAR == 0) {
         return sample(cx[c] + t);
+      } else if constexpr (NEAR == 3) {  // s = 1: neighbouring first taps
+        return near[t + c];
       } else {
         float v = near[t];
 #pragma unroll
@@ -253,7 +262,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
       }
     };
 #pragma unroll
-    for (int c = 0; c < kUpCols; ++c) {
+    for (int c = 0; c < COLS; ++c) {
       float a = 0.f;
 #pragma unroll
       for (int t = 0; t < 6; ++t) a += cw[c][t] * tap(c, t);
@@ -262,15 +271,23 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
   };
 #pragma unroll 2
   for (int e = wave; e < 4 * nseg + 5; e += 4) {
-    float o[kUpCols];
+    float o[COLS];
     interp(bb + e, o);
-    *reinterpret_cast<f4v *>(&hs[e][kUpCols * lane]) = f4v{o[0], o[1], o[2], o[3]};
+    if constexpr (COLS == 4) {
+      *reinterpret_cast<f4v *>(&hs[e][4 * lane]) = f4v{o[0], o[1], o[2], o[3]};
+    } else {
+      hs[e][lane] = o[0];
+    }
   }
   __syncthreads();
-  float win[6][kUpCols];
-  auto row_in = [&](int row, float (&o)[kUpCols]) {
-    const f4v v = *reinterpret_cast<const f4v *>(&hs[row - bb][kUpCols * lane]);
-    o[0] = v.x, o[1] = v.y, o[2] = v.z, o[3] = v.w;
+  float win[6][COLS];
+  auto row_in = [&](int row, float (&o)[COLS]) {
+    if constexpr (COLS == 4) {
+      const f4v v = *reinterpret_cast<const f4v *>(&hs[row - bb][4 * lane]);
+      o[0] = v.x, o[1] = v.y, o[2] = v.z, o[3] = v.w;
+    } else {
+      o[0] = hs[row - bb][lane];
+    }
   };
 #pragma unroll
   for (int t = 0; t < 5; ++t) row_in(b0 + t, win[t + 1]);
@@ -278,24 +295,17 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
 #pragma unroll
     for (int t = 0; t < 5; ++t)
 #pragma unroll
-      for (int c = 0; c < kUpCols; ++c) win[t][c] = win[t + 1][c];
+      for (int c = 0; c < COLS; ++c) win[t][c] = win[t + 1][c];
     row_in(b + 5, win[5]);
     const int lo = seg_lo(b, s);
     const int j0 = max(lo, 0), j1 = min(lo + s, nfy);
-    if (lane < s && lo + lane >= 0 && lo + lane < nfy) {
-      float w[6];
-      lanczos_taps(lo + lane, s, ncy, tt, w);
-#pragma unroll
-      for (int t = 0; t < 6; ++t) rws[wave][lane][t] = w[t];
-    }
-    wave_sync();
 #pragma unroll 4
     for (int j = j0; j < j1; ++j) {
-      const float *rw = rws[wave][j - lo];
+      const float *rw = rws[(b - bb) * s + j - lo];
       float *dst = out + (size_t)j * nfx + x0;
-      float a[kUpCols];
+      float a[COLS];
 #pragma unroll
-      for (int c = 0; c < kUpCols; ++c) {
+      for (int c = 0; c < COLS; ++c) {
         a[c] = 0.f;
 #pragma unroll
         for (int t = 0; t < 6; ++t) a[c] += rw[t] * win[t][c];
@@ -305,39 +315,41 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
           *reinterpret_cast<f4v *>(dst + 4 * lane) = f4v{a[0], a[1], a[2], a[3]};
       } else {
 #pragma unroll
-        for (int c = 0; c < kUpCols; ++c)
+        for (int c = 0; c < COLS; ++c)
           if (x0 + col(c) < nfx) dst[col(c)] = a[c];
       }
     }
-    wave_sync();
   }
 }
+static_assert(4 * up_max_seg(4, 1) * kUpMaxS <= kUpRows, "taps of a block's rows");
 
 // ---------------------------------------------------------------------------
 // Lanczos-3, adjoint.  The same walk with six coarse rows of partial sums: a
 // fine sample adds to all six, and when a segment ends its first row is
 // complete along y.  That row goes to LDS, where each thread sums the fine
-// columns of its coarse samples.  A block has kAdjSpan fine columns and the
-// coarse columns whose taps lie among them.  V4: a thread's fine columns are
+// columns of its coarse samples.  A block has SPAN fine columns and the
+// coarse columns whose taps lie among them; a thread has COLS of them, four, or
+// one where the map is that narrow (8000 x 8, s = 1: 24.8 -> 13.7 us, from the
+// taps of fewer columns and five blocks on a CU instead of three).  V4: a
+// thread's fine columns are
 // one 16-byte vector (rows start on 16-byte boundaries, and the block's first
 // column is rounded down to one).  2048^2, s = 8: 2255 -> 303 us (3.6 TB/s);
 // the former tile of 16 x 16 coarse samples read the fine map 1.9 times and
 // tested each of its samples for each coarse one.
 // ---------------------------------------------------------------------------
 constexpr int kAdjThreads = 256;
-constexpr int kAdjCols = 4;
-constexpr int kAdjSpan = kAdjThreads * kAdjCols;
 constexpr int kAdjMaxRows = 560;  // fine rows of a block, (rows + 5) s: three blocks share a CU
 
 // coarse columns per block: the fine columns from seg_lo(k0 - 5) to the end
 // of segment k0 + n - 1
-__host__ __device__ constexpr int adj_groups(int s) { return (kAdjSpan - 3) / s; }
-__host__ __device__ constexpr int adj_cols(int s) { return adj_groups(s) - 5; }
+__host__ __device__ constexpr int adj_groups(int s, int cols) { return (kAdjThreads * cols - 3) / s; }
+__host__ __device__ constexpr int adj_cols(int s, int cols) { return adj_groups(s, cols) - 5; }
 
-template <bool V4>
+template <bool V4, int COLS = 4>
 __global__ __launch_bounds__(kAdjThreads) void k_up_lanczos_adj(int ncy, int ncx, int s, int nrow,
                                                                 const float *__restrict__ g,
                                                                 float *__restrict__ out) {
+  constexpr int SPAN = kAdjThreads * COLS;
   const int nfy = ncy * s, nfx = ncx * s;
   __shared__ TapTable tt;
   // taps of the block's fine rows, and of its fine columns; column x of the
@@ -345,11 +357,11 @@ __global__ __launch_bounds__(kAdjThreads) void k_up_lanczos_adj(int ncy, int ncx
   // odd pitch) so that threads of neighbouring coarse
   // columns read neighbouring words
   __shared__ __align__(16) float rw[kAdjMaxRows][8];
-  __shared__ float cw[6][kAdjSpan + 16], vs[2][kAdjSpan + 16];
+  __shared__ float cw[6][SPAN + 16], vs[2][SPAN + 16];
   const int i0 = blockIdx.y * nrow, i1 = min(i0 + nrow, ncy);
-  const int kc = adj_cols(s), k0 = blockIdx.x * kc, k1 = min(k0 + kc, ncx);
+  const int kc = adj_cols(s, COLS), k0 = blockIdx.x * kc, k1 = min(k0 + kc, ncx);
   const int j00 = seg_lo(i0 - 5, s), x00 = seg_lo(k0 - 5, s);
-  const int ng = adj_groups(s), pitch = ng | 1;
+  const int ng = adj_groups(s, COLS), pitch = ng | 1;
   const int tid = threadIdx.x;
   tap_table_fill(tt, s);
   for (int e = tid; e < (i1 - i0 + 5) * s; e += kAdjThreads) {
@@ -366,17 +378,17 @@ __global__ __launch_bounds__(kAdjThreads) void k_up_lanczos_adj(int ncy, int ncx
   // this thread's fine columns: where they are read, whether they count, and
   // their words of vs (a spare one for columns outside the block's groups)
   const int xa = V4 ? x00 & ~3 : x00;  // rounds towards minus infinity
-  int xc[kAdjCols], at[kAdjCols];
-  bool in[kAdjCols];
+  int xc[COLS], at[COLS];
+  bool in[COLS];
 #pragma unroll
-  for (int c = 0; c < kAdjCols; ++c) {
-    const int x = xa + (V4 ? kAdjCols * tid + c : tid + c * kAdjThreads), e = x - x00;
+  for (int c = 0; c < COLS; ++c) {
+    const int x = xa + (V4 ? COLS * tid + c : tid + c * kAdjThreads), e = x - x00;
     in[c] = x >= 0 && x < nfx;
     xc[c] = in[c] ? x : 0;
-    at[c] = e >= 0 && e < ng * s ? (e % s) * pitch + e / s : kAdjSpan + 15;
+    at[c] = e >= 0 && e < ng * s ? (e % s) * pitch + e / s : SPAN + 15;
   }
   __syncthreads();
-  float acc[6][kAdjCols] = {};
+  float acc[6][COLS] = {};
   for (int b = i0 - 5; b < i1; ++b) {
     const int lo = seg_lo(b, s);
     const int j0 = max(lo, 0), j1 = min(lo + s, nfy);
@@ -384,25 +396,25 @@ __global__ __launch_bounds__(kAdjThreads) void k_up_lanczos_adj(int ncy, int ncx
     for (int j = j0; j < j1; ++j) {
       const float *row = g + (size_t)j * nfx;
       const float *w = rw[j - j00];
-      float v[kAdjCols];
+      float v[COLS];
 #pragma unroll
-      for (int c = 0; c < kAdjCols; ++c)
+      for (int c = 0; c < COLS; ++c)
         if constexpr (!V4) v[c] = row[xc[c]];
       if constexpr (V4) {
         const f4v q = *reinterpret_cast<const f4v *>(row + xc[0]);
         v[0] = q.x, v[1] = q.y, v[2] = q.z, v[3] = q.w;
       }
 #pragma unroll
-      for (int c = 0; c < kAdjCols; ++c) v[c] = in[c] ? v[c] : 0.f;
+      for (int c = 0; c < COLS; ++c) v[c] = in[c] ? v[c] : 0.f;
 #pragma unroll
       for (int t = 0; t < 6; ++t)
 #pragma unroll
-        for (int c = 0; c < kAdjCols; ++c) acc[t][c] += w[t] * v[c];
+        for (int c = 0; c < COLS; ++c) acc[t][c] += w[t] * v[c];
     }
     if (b >= i0) {
       float *line = vs[b & 1];  // the other line may still be read
 #pragma unroll
-      for (int c = 0; c < kAdjCols; ++c) line[at[c]] = acc[0][c];
+      for (int c = 0; c < COLS; ++c) line[at[c]] = acc[0][c];
       __syncthreads();
       // coarse column k takes tap t of the columns of segment k - t, which is
       // group k - t - (k0 - 5)
@@ -420,7 +432,7 @@ __global__ __launch_bounds__(kAdjThreads) void k_up_lanczos_adj(int ncy, int ncx
 #pragma unroll
     for (int t = 0; t < 6; ++t)
 #pragma unroll
-      for (int c = 0; c < kAdjCols; ++c) acc[t][c] = t < 5 ? acc[t + 1][c] : 0.f;
+      for (int c = 0; c < COLS; ++c) acc[t][c] = t < 5 ? acc[t + 1][c] : 0.f;
   }
 }
 
@@ -443,12 +455,22 @@ hipError_t launch_upsample(int kind, int ncy, int ncx, int s, const float *coars
       hipLaunchKernelGGL(k_up_nearest<1>, grid, dim3(256), 0, stream, ncy, ncx, s, coarse, fine);
   } else {
     // ncy + 2 segments of rows, 4 nseg per block (whose LDS starts with five
-    // more rows): fewer while the chip has not four blocks for each CU
-    int nseg = kUpMaxSeg;
-    while (nseg > 1 && (long long)cdiv(nfx, kUpSpan) * cdiv(ncy + 2, 4 * nseg) < 1024) nseg /= 2;
-    const dim3 grid(cdiv(nfx, kUpSpan), cdiv(ncy + 2, 4 * nseg));
+    // more rows): fewer while the chip has not two or three blocks for each CU
+    // (at 1024 blocks and more a second, partly filled round of them began:
+    // 600 x 599, s = 2, 722 blocks 9.3 us, 1444 blocks 11.4)
     const bool v4 = nfx % 4 == 0 && aligned16(fine);
-    const auto kernel = !v4      ? k_up_lanczos<false, 0>
+    auto blocks = [&](int cols, int n) { return (long long)cdiv(nfx, 64 * cols) * cdiv(ncy + 2, 4 * n); };
+    // One column per thread where four leave lanes or CUs without work, and
+    // where rows are not whole 16-byte vectors up to s = 4 (us of 4 -> 1
+    // columns: 500 x 333, s = 3, 11.5 -> 7.9; 8000 x 48, s = 2, 17.9 -> 9.8;
+    // 4000 x 3999, s = 2, 326 -> 215; but 2047^2, s = 5, 222 -> 243)
+    const bool small = blocks(4, 1) < 640 || nfx <= 192;
+    const int cols = small || (!v4 && (s <= 4 || blocks(4, 1) < 8192)) ? 1 : 4;
+    int nseg = up_max_seg(cols, s);
+    while (nseg > 1 && blocks(cols, nseg) < 640) nseg /= 2;
+    const dim3 grid(cdiv(nfx, 64 * cols), cdiv(ncy + 2, 4 * nseg));
+    const auto kernel = cols == 1 ? k_up_lanczos<false, 0, 1>
+                        : !v4    ? k_up_lanczos<false, 0>
                         : s >= 3 ? k_up_lanczos<true, 1>
                         : s == 2 ? k_up_lanczos<true, 2>
                                  : k_up_lanczos<true, 3>;
@@ -474,12 +496,15 @@ hipError_t launch_upsample_adjoint(int kind, int ncy, int ncx, int s, const floa
     // nrow coarse rows per block: up to 64 (five segments of lead-in each),
     // as many as their taps' LDS holds, fewer while the grid has less than
     // two blocks for each CU
-    const unsigned bx = cdiv(ncx, adj_cols(s));
+    const bool narrow = ncx <= adj_cols(s, 1);
+    const unsigned bx = cdiv(ncx, adj_cols(s, narrow ? 1 : 4));
     int nrow = kAdjMaxRows / s - 5;
     if (nrow > 64) nrow = 64;
     while (nrow > 4 && bx * cdiv(ncy, nrow) < 512) nrow = (nrow + 1) / 2;
     const dim3 grid(bx, cdiv(ncy, nrow)), t(kAdjThreads);
-    if (ncx * s % 4 == 0 && aligned16(grad_fine))
+    if (narrow)
+      hipLaunchKernelGGL((k_up_lanczos_adj<false, 1>), grid, t, 0, stream, ncy, ncx, s, nrow, grad_fine, grad_coarse);
+    else if (ncx * s % 4 == 0 && aligned16(grad_fine))
       hipLaunchKernelGGL(k_up_lanczos_adj<true>, grid, t, 0, stream, ncy, ncx, s, nrow, grad_fine, grad_coarse);
     else
       hipLaunchKernelGGL(k_up_lanczos_adj<false>, grid, t, 0, stream, ncy, ncx, s, nrow, grad_fine, grad_coarse);
