@@ -374,7 +374,9 @@ dop_status dop_serve_submit(dop_server *srv, const dop_problem *prob,
 /* Scheduling policies.
  *   DOP_SERVE_CHUNKED (default): a request runs in chunks of one wavelength
  *     group (up to four wavelengths; its workspace holds that many fields,
- *     at most half the arena, or as many fields as fit at admission).
+ *     at most half the arena, or as many fields as fit at admission), or,
+ *     where dop_psf does not group wavelengths, of up to four that hold under
+ *     1e8 padded pixels x wavelengths, in one field.
  *     All chunks go through one in-order stream, two enqueued at a time
  *     (up to eight while those hold under 1e8 padded pixels x wavelengths,
  *     about a millisecond of work); each time a chunk completes, the next
@@ -423,6 +425,7 @@ dop_status dop_serve_destroy(dop_server *srv);
  * Its streams are in-order queues of wall time: a chunk of k wavelengths
  * (a whole request under FIFO / SIZE_AWARE) occupies its stream for
  * service_us_per_mpix * (k * my * m / 1e6) microseconds and writes nothing.
+ * Chunks take up to four wavelengths, a field each, on every grid.
  * `arena` is only used as an address range (may be any non-NULL value).
  * For CPU tests of admission, scheduling, budget, order and shutdown; needs
  * no GPU.

@@ -317,16 +317,23 @@ dop_status check_ctx_device(const dop_context *ctx) {
   return DOP_OK;
 }
 
-int psf_group(const dop_problem *prob, const void *saved_u, size_t ws_bytes) {
-  const bool small = route_of(prob, IN_PHASE) == ROUTE_SMALL;
-  if (saved_u && !small) return 1;
-  const size_t field = workspace_bytes(prob);
+// Wavelengths per group of a PSF or a gradient (by its input mode) when the
+// workspace sets no limit.
+static int group_limit(const dop_problem *prob, InMode in, bool save_fields) {
   const int plan = plan_id(grid_cols(prob), grid_rows(prob));
-  const int g = small ? small_max_group(plan) : plan_max_group(plan);
-  const size_t fit = ws_bytes / field;
-  int r = prob->n_lambda < g ? prob->n_lambda : g;
-  if (fit < (size_t)r) r = (int)fit;
-  return r < 1 ? 1 : r;
+  int g = 1;
+  switch (route_of(prob, in)) {
+    case ROUTE_SMALL: g = small_max_group(plan); break;
+    case ROUTE_FIVE: g = in == IN_PHASE && !save_fields ? plan_max_group(plan) : 1; break;
+    case ROUTE_TRI: break;
+  }
+  return prob->n_lambda < g ? prob->n_lambda : g;
+}
+
+int psf_group(const dop_problem *prob, const void *saved_u, size_t ws_bytes) {
+  const int g = group_limit(prob, IN_PHASE, saved_u != nullptr);
+  const size_t fit = ws_bytes / workspace_bytes(prob);
+  return fit >= (size_t)g ? g : fit < 1 ? 1 : (int)fit;
 }
 
 // Whether passes launched now are timed one by one.
@@ -364,12 +371,11 @@ dop_status enqueue_psf_range(const dop_context *ctx, const dop_problem *prob, in
     kp.psf = psf;
   };
   for (int k0 = kbeg; k0 < kend;) {
-    int gk = kend - k0 < g ? kend - k0 : g;
+    const int gk = kend - k0 < g ? kend - k0 : g;
     KParams kp;
     setup(kp, k0, ws);
     kp.first = (k0 == 0);
     kp.saved_out = saved_u ? static_cast<float2 *>(saved_u) + (size_t)k0 * nn : nullptr;
-    if (kp.route == ROUTE_TRI) gk = 1;
     kp.group = gk;
     for (int q = 1; q < gk; ++q) {
       KParams kq;
@@ -695,13 +701,10 @@ dop_status dop_psf_backward(dop_context *ctx, const dop_problem *prob, const flo
   if ((s = check_ctx_device(ctx)) != DOP_OK) return s;
   const size_t nn = (size_t)doe_rows(prob) * prob->n;
   const int up = upsample_factor(prob);
-  // wavelengths per launch: as many as the workspace has fields for on the
-  // small-grid path, else one
-  int g = 1;
-  if (route_of(prob, IN_GRAD) == ROUTE_SMALL && !one_by_one(ctx, prob, true))
-    while (g < small_max_group(plan_id(grid_cols(prob), grid_rows(prob))) && g < prob->n_lambda &&
-           workspace_bytes_op(prob, DOP_OP_PSF_BACKWARD, g + 1) <= ws_bytes)
-      ++g;
+  // wavelengths per launch: as many as the workspace has fields for, at most
+  // the path's limit
+  int g = one_by_one(ctx, prob, true) ? 1 : group_limit(prob, IN_GRAD, false);
+  while (g > 1 && workspace_bytes_op(prob, DOP_OP_PSF_BACKWARD, g) > ws_bytes) --g;
   // with an upsampled design the passes accumulate the n x n fine gradient in
   // the workspace tail; its s x s block sums are the coarse gradient
   float *grad_fine =

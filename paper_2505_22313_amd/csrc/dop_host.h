@@ -42,8 +42,10 @@ dop_status enqueue_psf_range(const dop_context *ctx, const dop_problem *prob, in
                              size_t ws_bytes, hipStream_t stream, bool timed = true);
 
 // Wavelengths per group that dop_psf uses for `prob` with a workspace of
-// ws_bytes: as many whole fields as fit, at most the plan's limit and the
-// wavelength count, and 1 when the fields are saved.
+// ws_bytes: as many whole fields as fit, at most the wavelength count and what
+// the passes that the problem takes can run together (1 on the three-pass path
+// of half-filled planes, on grids whose last pass ends in a radix-67 stage, and
+// on the five passes when the fields are saved).
 int psf_group(const dop_problem *prob, const void *saved_u, size_t ws_bytes);
 
 int context_device(const dop_context *ctx);

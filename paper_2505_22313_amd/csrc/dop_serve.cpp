@@ -8,7 +8,8 @@
 //
 //  - DOP_SERVE_CHUNKED (default): a request's wavelengths run in chunks of
 //    one wavelength group (up to four wavelengths that share one read of the
-//    heights and one read-modify-write of the PSF).  Chunks of all admitted
+//    heights and one read-modify-write of the PSF; where the passes take one
+//    wavelength at a time, one, or a few short ones).  Chunks of all admitted
 //    requests go through one in-order stream, two enqueued at a time (more
 //    while they hold under about a millisecond of work).  Each time a chunk
 //    completes, the next one is taken from the admitted request with the
@@ -79,7 +80,7 @@ struct Request {
   float *psf = nullptr;
   size_t field = 0;      // bytes of one workspace field
   size_t need = 0;       // workspace bytes held while admitted
-  int group = 1;         // wavelengths per chunk (fields in the workspace)
+  int chunk = 1;         // wavelengths per chunk
   bool chunked = false;  // admitted under DOP_SERVE_CHUNKED
   double t_submit = 0, t_done = 0;
   dop_status status = DOP_NOT_READY;
@@ -145,6 +146,9 @@ class Executor {
  public:
   virtual ~Executor() = default;
   virtual void thread_init() {}
+  // Wavelengths that the request runs together, each in a workspace field of
+  // its own, when the arena sets no limit.
+  virtual int group(const Request &r) const = 0;
   virtual dop_status start(int lane, Request &r, int k0, int k1, void *ws, size_t ws_bytes,
                            int *token) = 0;
   virtual bool done(int token, dop_status *st) = 0;
@@ -193,6 +197,7 @@ class GpuExecutor : public Executor {
       if (s) (void)hipStreamDestroy(s);
   }
   void thread_init() override { (void)hipSetDevice(context_device(ctx_)); }
+  int group(const Request &r) const override { return psf_group(&r.prob, nullptr, (size_t)-1); }
   dop_status start(int lane, Request &r, int k0, int k1, void *ws, size_t ws_bytes,
                    int *token) override {
     int t = 0;
@@ -233,6 +238,8 @@ class MockExecutor : public Executor {
  public:
   MockExecutor(int lanes, int tokens, double us_per_mpix)
       : lane_end_(lanes, 0.0), tok_end_(tokens, 0.0), pool_(tokens), us_per_mpix_(us_per_mpix) {}
+  // (whatever the grid: which grids group is the GPU path's matter)
+  int group(const Request &r) const override { return std::min(r.prob.n_lambda, 4); }
   dop_status start(int lane, Request &r, int k0, int k1, void *, size_t, int *token) override {
     int t = 0;
     if (!pool_.take(&t)) return fail(DOP_ERR_DEVICE, "no completion token free");
@@ -351,9 +358,9 @@ struct dop_server {
     // whole-request policies run one wavelength at a time in one field; the
     // chunked policy gives a request up to a wavelength group of fields, at
     // most half the arena, or as many fields as fit now (at least one)
-    int g = 1;
+    int g = 1, limit = 1;
     if (ch) {
-      g = psf_group(&r->prob, nullptr, (size_t)-1);
+      g = limit = ex->group(*r);
       while (g > 1 && Arena::round((size_t)g * r->field) > arena.size() / 2) --g;
     }
     size_t off = 0;
@@ -361,7 +368,14 @@ struct dop_server {
       if (g == 1) return false;
       --g;
     }
-    r->group = g;
+    r->chunk = g;
+    // wavelengths that run one at a time in one field: a few per chunk where
+    // they are short, so that the scheduler keeps up with them (4096^2, three
+    // at 87 us: 3 % of the throughput)
+    if (limit == 1)
+      while (r->chunk < std::min(4, r->prob.n_lambda) &&
+             (r->chunk + 1) * work(*r) < kMinQueued * r->prob.n_lambda)
+        ++r->chunk;
     r->need = (size_t)g * r->field;
     r->off = off;
     r->slot = s;
@@ -440,7 +454,7 @@ struct dop_server {
     while (on_lane0 < kDepth || (on_lane0 < kMaxDepth && queued < kMinQueued)) {
       Request *r = pick(now);
       if (!r) return;
-      const int k1 = std::min(r->prob.n_lambda, r->k_next + r->group);
+      const int k1 = std::min(r->prob.n_lambda, r->k_next + r->chunk);
       const double w = (double)(k1 - r->k_next) * grid_cols(&r->prob) * (double)grid_rows(&r->prob);
       const size_t before = chunks.size();
       start_chunk(r, k1, 0);
