@@ -160,6 +160,17 @@ dop_status dop_workspace_size(const dop_context *ctx, const dop_problem *prob,
                               int op, size_t *bytes);
 
 /*
+ * Workspace of an operation that is to run up to *group wavelengths together
+ * (*group >= 1; see "Wavelength groups" below).  On return *group is the
+ * number it runs together given *bytes of workspace: at most as asked, at most
+ * K, and 1 where the passes that `prob` takes do not group wavelengths.
+ * save_fields != 0: dop_psf with saved_u (ignored by the other operations).
+ * With *group = 1, *bytes is dop_workspace_size's.  Pure host call.
+ */
+dop_status dop_workspace_size_group(const dop_context *ctx, const dop_problem *prob, int op,
+                                    int save_fields, int *group, size_t *bytes);
+
+/*
  * Eq. (3) for one wavelength index k (0 <= k < K; lambda[k] is used, n_index
  * and weight are ignored): propagates the N x N c64 field `u_in` (zero-padded
  * to M x M at p0) by z.  `u_out` receives N x N c64 (CROP) or M x M c64

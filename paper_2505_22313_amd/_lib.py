@@ -105,6 +105,9 @@ _SIGNATURES = {
     "dop_context_create": (ctypes.c_int, [ctypes.c_int, ctypes.POINTER(_VP)]),
     "dop_context_destroy": (ctypes.c_int, [_VP]),
     "dop_workspace_size": (ctypes.c_int, [_VP, _PROB, ctypes.c_int, ctypes.POINTER(ctypes.c_size_t)]),
+    "dop_workspace_size_group": (ctypes.c_int, [_VP, _PROB, ctypes.c_int, ctypes.c_int,
+                                                ctypes.POINTER(ctypes.c_int),
+                                                ctypes.POINTER(ctypes.c_size_t)]),
     "dop_propagate": (ctypes.c_int, [_VP, _PROB, ctypes.c_int, _VP, _VP, _VP, ctypes.c_size_t, _VP]),
     "dop_psf": (ctypes.c_int, [_VP, _PROB, _VP, _VP, _VP, _VP, _VP, ctypes.c_size_t, _VP]),
     "dop_psf_noalloc": (ctypes.c_int, [_VP, _PROB, _VP, _VP, _VP, _VP, _VP]),

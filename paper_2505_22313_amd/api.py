@@ -52,7 +52,7 @@ class Problem:
             raise ValueError("out_mode must be 'crop' or 'full'")
         self.out_mode = out_mode
         self.bandlimit = bool(bandlimit)
-        self._ws_bytes = {}  # workspace_size's results: op -> (extents, bytes)
+        self._ws_bytes = {}  # group_workspace_size's results by what they follow from
         self._c = DopProblem()
         c = self._c
         c.n, c.m, c.dx, c.z = self.nx, self.mx, self.dx, self.z
@@ -98,18 +98,26 @@ class Problem:
         return ctypes.byref(self._c)
 
 
-def workspace_size(prob, op=L.DOP_OP_PSF):
-    # the size follows from the extents alone, so it is asked for again only
-    # when they have changed (each call checks the whole problem by itself)
+def group_workspace_size(prob, op, group=4, save_fields=False):
+    """(wavelengths run together, bytes of workspace for them) of an operation
+    that may run up to `group` together."""
+    # both follow from the extents, the window and the wavelength count alone,
+    # so they are asked for again only when those have changed (each call
+    # checks the whole problem by itself)
     c = prob._c
-    key = (c.n, c.m, c.ny, c.my, c.upsample)
-    known = prob._ws_bytes.get(op)
-    if known is not None and known[0] == key:
-        return known[1]
-    out = ctypes.c_size_t(0)
-    check(lib().dop_workspace_size(None, prob.ptr(), op, ctypes.byref(out)), "dop_workspace_size")
-    prob._ws_bytes[op] = (key, out.value)
-    return out.value
+    key = (op, group, save_fields, c.n, c.m, c.ny, c.my, c.upsample, c.n_lambda, c.out_mode)
+    known = prob._ws_bytes.get(key)
+    if known is None:
+        g, out = ctypes.c_int(group), ctypes.c_size_t(0)
+        check(lib().dop_workspace_size_group(None, prob.ptr(), op, 1 if save_fields else 0,
+                                             ctypes.byref(g), ctypes.byref(out)),
+              "dop_workspace_size_group")
+        known = prob._ws_bytes[key] = (g.value, out.value)
+    return known
+
+
+def workspace_size(prob, op=L.DOP_OP_PSF):
+    return group_workspace_size(prob, op, 1)[1]
 
 
 class Context:
@@ -233,40 +241,37 @@ def propagate(u_in, prob, k=0, ctx=None, out=None):
     return out
 
 
-# Fields up to this size are grouped without asking how much memory is free
-# (four of them are a thousandth of the card's memory): small grids run
-# several wavelengths per launch given the fields.
-_SMALL_FIELD = 64 << 20
+# Groups up to this size are taken without asking how much memory is free (a
+# thousandth of the card's): small grids run several wavelengths per launch
+# given the fields.
+_SMALL_GROUP = 256 << 20
 
 
-def _grouped_workspace(ctx, stream, nbytes, field, g):
-    """Workspace of nbytes plus g - 1 more fields, or as many of them as can
-    be allocated; returns (workspace, its usable bytes)."""
-    while g > 1:
+def _workspace(ctx, prob, op, stream, group=4, save_fields=False):
+    """Workspace of dop_psf or dop_psf_backward: one field, or room for as many
+    wavelengths together (up to `group`) as the operation runs and the memory
+    holds.  Returns (workspace, its usable bytes)."""
+    g, nbytes = group_workspace_size(prob, op, max(1, int(group)), save_fields)
+    if g > 1 and (nbytes > _SMALL_GROUP or ctx.group_cap):
+        field = workspace_size(prob, L.DOP_OP_PSF)
+        fits = ctx.group_cap.get(field, g)
+        if nbytes > _SMALL_GROUP:
+            # what the device could hold: free memory, blocks torch keeps
+            # cached, and this stream's workspace (replaced below), less a margin
+            free, _ = torch.cuda.mem_get_info(ctx.device)
+            spare = torch.cuda.memory_reserved(ctx.device) - torch.cuda.memory_allocated(ctx.device)
+            budget = free + spare + ctx.workspace_bytes(stream) - (4 << 30)
+            fits = min(fits, budget // field)
+        g, nbytes = group_workspace_size(prob, op, max(1, min(g, fits)), save_fields)
+    while True:
         try:
-            return ctx.workspace(nbytes + (g - 1) * field, stream), nbytes + (g - 1) * field
+            return ctx.workspace(nbytes, stream), nbytes
         except torch.cuda.OutOfMemoryError:
-            g -= 1
-            ctx.group_cap[field] = g  # do not try the larger group again
-    return ctx.workspace(nbytes, stream), nbytes
-
-
-def _psf_workspace(ctx, prob, stream, save_fields, group):
-    """Workspace for dop_psf: one field, or room for a group of up to `group`
-    wavelengths (the library then reads h and read-modify-writes the PSF once
-    per group) when the memory is free and, on larger grids, the fields are
-    not saved."""
-    field = workspace_size(prob, L.DOP_OP_PSF)
-    small = field <= _SMALL_FIELD
-    g = 1 if save_fields and not small else max(1, min(int(group), prob.k, ctx.group_cap.get(field, 4)))
-    if g > 1 and not small:
-        # what the device could hold: free memory, blocks torch keeps cached,
-        # and this stream's workspace (replaced below), less a margin
-        free, _ = torch.cuda.mem_get_info(ctx.device)
-        spare = torch.cuda.memory_reserved(ctx.device) - torch.cuda.memory_allocated(ctx.device)
-        budget = free + spare + ctx.workspace_bytes(stream) - (4 << 30)
-        g = max(1, min(g, budget // field))
-    return _grouped_workspace(ctx, stream, field, field, g)
+            if g == 1:
+                raise
+            # do not try the larger group again
+            ctx.group_cap[workspace_size(prob, L.DOP_OP_PSF)] = g - 1
+            g, nbytes = group_workspace_size(prob, op, g - 1, save_fields)
 
 
 def psf(h, prob, amp=None, save_fields=False, ctx=None, out=None, group=4):
@@ -286,7 +291,7 @@ def psf(h, prob, amp=None, save_fields=False, ctx=None, out=None, group=4):
     if save_fields:
         saved = torch.empty((prob.k,) + prob.doe_shape, dtype=torch.complex64, device=h.device)
     stream = _stream_handle(dev)
-    ws, nbytes = _psf_workspace(ctx, prob, stream, save_fields, group)
+    ws, nbytes = _workspace(ctx, prob, L.DOP_OP_PSF, stream, group, save_fields)
     check(lib().dop_psf(ctx.handle, prob.ptr(), _ptr(h), _ptr(amp), _ptr(out), _ptr(saved),
                         _ptr(ws), nbytes, stream), "dop_psf")
     return (out, saved) if save_fields else out
@@ -326,13 +331,9 @@ def psf_backward(h, prob, saved_u, grad_psf, amp=None, ctx=None, out=None):
         out = torch.empty(prob.h_shape, dtype=torch.float32, device=h.device)
     _need(out, "out", torch.float32, prob.h_shape, dev)
     stream = _stream_handle(dev)
-    nbytes = workspace_size(prob, L.DOP_OP_PSF_BACKWARD)
-    field = 8 * prob.my * (prob.mx + 16)
-    g = min(prob.k, ctx.group_cap.get(field, 4)) if field <= _SMALL_FIELD else 1
-    # (fields of a group end on a 256-byte boundary before the fine gradient)
-    ws, _ = _grouped_workspace(ctx, stream, nbytes + (256 if g > 1 else 0), field, g)
+    ws, nbytes = _workspace(ctx, prob, L.DOP_OP_PSF_BACKWARD, stream)
     check(lib().dop_psf_backward(ctx.handle, prob.ptr(), _ptr(h), _ptr(amp), _ptr(saved_u),
-                                 _ptr(grad_psf), _ptr(out), _ptr(ws), ws.numel(),
+                                 _ptr(grad_psf), _ptr(out), _ptr(ws), nbytes,
                                  stream), "dop_psf_backward")
     return out
 

@@ -600,6 +600,21 @@ dop_status dop_workspace_size(const dop_context *ctx, const dop_problem *prob, i
   return DOP_OK;
 }
 
+dop_status dop_workspace_size_group(const dop_context *ctx, const dop_problem *prob, int op,
+                                    int save_fields, int *group, size_t *bytes) {
+  clear_error();
+  if (!group || !bytes) return fail(DOP_ERR_INVALID_ARG, "group / bytes is NULL");
+  if (*group < 1) return fail(DOP_ERR_INVALID_ARG, "group must be >= 1 (got %d)", *group);
+  size_t one = 0;
+  const dop_status s = dop_workspace_size(ctx, prob, op, &one);
+  if (s != DOP_OK) return s;
+  const int limit = op == DOP_OP_PROPAGATE ? 1
+                    : group_limit(prob, op == DOP_OP_PSF ? IN_PHASE : IN_GRAD, save_fields != 0);
+  if (*group > limit) *group = limit;
+  *bytes = *group == 1 ? one : workspace_bytes_op(prob, op, *group);
+  return DOP_OK;
+}
+
 static dop_status check_ws(const dop_problem *prob, int op, void *ws, size_t ws_bytes) {
   if (!ws) return fail(DOP_ERR_WORKSPACE, "workspace is NULL");
   if (ws_bytes < workspace_bytes_op(prob, op))
