@@ -155,8 +155,8 @@ hipError_t launch_small(const KParams &p, hipStream_t stream, hipEvent_t *ev);
 // window; tri_pitch
 // gives KParams::pitch3 for a number of rows; launch_tri enqueues one
 // wavelength in any input and output mode, with ev[0..3] (if not NULL)
-// recorded before, between and after its passes.  It needs the workspace of
-// one field.
+// recorded before, between and after its passes, and refuses any other
+// problem or group.  It needs the workspace of one field.
 int tri_grid(int plan);  // points per side if the plan may take the path, else 0
 bool tri_path(int plan, int n, int rows, bool full);
 int tri_pitch(int plan, int nrows);

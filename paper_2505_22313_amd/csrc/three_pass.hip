@@ -693,6 +693,9 @@ int tri_pitch(int plan, int nrows) {
 }
 
 hipError_t launch_tri(const KParams &p, hipStream_t s, hipEvent_t *ev) {
+  // the kernels run one wavelength, in the window and half planes of tri_path
+  if (p.group != 1 || p.nrows_out != p.nrows_in || !tri_path(p.plan, p.n, p.nrows_in, p.full))
+    return hipErrorInvalidValue;
   switch (p.plan) {
     case 12: return launch_lm<12>(p, s, ev);
     case 13: return launch_lm<13>(p, s, ev);

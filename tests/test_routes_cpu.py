@@ -60,3 +60,10 @@ def check(tmp_path_factory):
 def test_route(check, my, mx, ny, nx, k, full, psf, field, gradient):
     got = check(my, mx, ny, nx, k, full)
     assert (got["psf"], got["field"], got["gradient"]) == (psf, field, gradient)
+
+
+def test_three_pass_launcher_refuses_what_its_kernels_do_not_run(check):
+    """A group of wavelengths (its kernels would skip all but the first) and
+    problems outside the half planes, before anything is launched."""
+    got = check("refuse")
+    assert got and all(v == "1" for v in got.values()), got
