@@ -6,7 +6,7 @@ same process (bench.py --calib-copy: 4 GiB read + 4 GiB written by the
 runtime's copy kernel).  The result is bytes per launch, keyed by the hash of
 the kernel source it was measured on, so a stale figure is never reported.
 
-    python -m paper_2505_22313_amd.profiling traffic <fetch_dir> <write_dir>
+    python -m paper_2505_22313_amd.profiling traffic <fetch_dir> <write_dir> [<n>]
     python -m paper_2505_22313_amd.profiling stats <trace_dir>
 """
 
@@ -15,6 +15,7 @@ import glob
 import hashlib
 import json
 import os
+import re
 import sys
 from collections import defaultdict
 
@@ -22,6 +23,12 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 KERNEL_SOURCE = os.path.join(HERE, "csrc", "asm_kernels.hip")
 CALIB_KERNEL = "__amd_rocclr_copyBuffer"
 CALIB_BYTES = 4 * 1024 ** 3
+
+COMMAND = ("rocprofv3 --pmc FETCH_SIZE --kernel-trace --output-format csv -d gpurun_out/fetch -o run -- "
+           "python3 bench.py --steps 1 --warmup 0 --no-cpu-baseline --no-serve --no-design "
+           "--no-variants --lambdas 2 --calib-copy; the same with --pmc WRITE_SIZE -d "
+           "gpurun_out/write; then python -m paper_2505_22313_amd.profiling traffic "
+           "gpurun_out/fetch gpurun_out/write 32768")
 
 PASS_NAMES = {"k_pass_a_fwd": "pass_a_fwd", "k_pass_b_fwd": "pass_b_fwd", "k_pass_c": "pass_c",
               "k_pass_b_inv": "pass_b_inv", "k_pass_a_inv": "pass_a_inv"}
@@ -37,6 +44,11 @@ def pass_name(kernel_name):
         if "dop::" + k + "<" in kernel_name:
             return v
     return None
+
+
+def plan_of(kernel_name):
+    """Plan id (first template argument) of a pass kernel."""
+    return int(re.search(r"dop::k_pass_\w+<(\d+)", kernel_name).group(1))
 
 
 def _csv(directory, suffix):
@@ -55,7 +67,10 @@ def counters(directory):
     return out
 
 
-def traffic(fetch_dir, write_dir):
+def traffic(fetch_dir, write_dir, n=None):
+    """Calibrated bytes per launch of each pass of the one grid the counters
+    were taken on: square, a power of two m (plan ids below 100 are log2 m).
+    n: the DOE's side, recorded beside m."""
     f = counters(fetch_dir)
     w = counters(write_dir)
     fk = [v for k, v in f.items() if k.startswith(CALIB_KERNEL)]
@@ -64,7 +79,13 @@ def traffic(fetch_dir, write_dir):
         raise RuntimeError("calibration copy kernel not found: run bench.py with --calib-copy")
     f_factor = CALIB_BYTES / (1024.0 * max(fk[0]["FETCH_SIZE"]))
     w_factor = CALIB_BYTES / (1024.0 * max(wk[0]["WRITE_SIZE"]))
-    res = {"source_sha": kernel_source_hash(), "fetch_factor": round(f_factor, 4),
+    plans = {plan_of(k) for k in f if pass_name(k)}
+    if len(plans) != 1 or min(plans) >= 100:
+        raise RuntimeError(f"counters of one power-of-two grid wanted, found plans {sorted(plans)}")
+    res = {"source_sha": kernel_source_hash(), "m": 1 << plans.pop(), "n": n, "command": COMMAND,
+           "calibration": f"4 GiB device copy by the runtime's copy kernel ({CALIB_KERNEL}, its "
+                          "largest dispatch) in the same process: bytes moved / bytes counted",
+           "fetch_factor": round(f_factor, 4),
            "write_factor": round(w_factor, 4), "kernels": {}}
     for k, v in f.items():
         name = pass_name(k)
@@ -86,7 +107,7 @@ def stats(trace_dir):
 
 def main(argv):
     if len(argv) >= 3 and argv[0] == "traffic":
-        print(json.dumps(traffic(argv[1], argv[2]), indent=1))
+        print(json.dumps(traffic(argv[1], argv[2], int(argv[3]) if len(argv) > 3 else None), indent=1))
     elif len(argv) >= 2 and argv[0] == "stats":
         print(json.dumps(stats(argv[1]), indent=1))
     else:
