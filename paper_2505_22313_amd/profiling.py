@@ -4,7 +4,7 @@ HBM traffic: `FETCH_SIZE` and `WRITE_SIZE` (KiB per dispatch) are scaled by
 what the same counters read for a plain device copy of known size run in the
 same process (bench.py --calib-copy: 4 GiB read + 4 GiB written by the
 runtime's copy kernel).  The result is bytes per launch, keyed by the hash of
-the kernel source it was measured on, so a stale figure is never reported.
+the sources its kernels are compiled from, so a stale figure is never reported.
 
     python -m paper_2505_22313_amd.profiling traffic <fetch_dir> <write_dir> [<n>]
     python -m paper_2505_22313_amd.profiling stats <trace_dir>
@@ -34,9 +34,30 @@ PASS_NAMES = {"k_pass_a_fwd": "pass_a_fwd", "k_pass_b_fwd": "pass_b_fwd", "k_pas
               "k_pass_b_inv": "pass_b_inv", "k_pass_a_inv": "pass_a_inv"}
 
 
+def kernel_sources(path=KERNEL_SOURCE):
+    """The source of the pass kernels and every file of the repository that it
+    includes, directly or not, in the order of inclusion."""
+    found = []
+
+    def visit(p):
+        p = os.path.normpath(p)
+        if p in found:
+            return
+        found.append(p)
+        with open(p) as f:
+            for name in re.findall(r'^\s*#\s*include\s+"([^"]+)"', f.read(), re.M):
+                visit(os.path.join(os.path.dirname(p), name))
+
+    visit(path)
+    return found
+
+
 def kernel_source_hash():
-    with open(KERNEL_SOURCE, "rb") as f:
-        return hashlib.sha256(f.read()).hexdigest()[:16]
+    h = hashlib.sha256()
+    for p in kernel_sources():
+        with open(p, "rb") as f:
+            h.update(f.read())
+    return h.hexdigest()[:16]
 
 
 def pass_name(kernel_name):

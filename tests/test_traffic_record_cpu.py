@@ -51,3 +51,24 @@ def test_counters_of_one_grid_only(tmp_path):
         pr.traffic(*write_run(tmp_path / "two", plans=(15, 16)))
     with pytest.raises(RuntimeError):
         pr.traffic(*write_run(tmp_path / "table", plans=(105,)))
+
+
+def test_source_hash_covers_what_the_kernels_include(tmp_path, monkeypatch):
+    """The hash follows the includes of the pass kernels' source: a change in
+    any of these files makes a recorded figure stale."""
+    names = {os.path.basename(p) for p in pr.kernel_sources()}
+    assert {"asm_kernels.hip", "asm_device.h", "asm_stages.h", "dop_internal.h"} <= names
+    files = {"a.hip": '#include <x.h>\n#include "b.h"\nint a;\n', "b.h": '  # include "sub/c.h"\n',
+             "sub/c.h": '#include "../b.h"\nint c;\n', "other.h": "int o;\n"}
+    (tmp_path / "sub").mkdir()
+    for name, text in files.items():
+        (tmp_path / name).write_text(text)
+    monkeypatch.setattr(pr.kernel_sources, "__defaults__", (str(tmp_path / "a.hip"),))
+    first = pr.kernel_source_hash()
+    (tmp_path / "other.h").write_text("int p;\n")
+    assert pr.kernel_source_hash() == first
+    for name in ("a.hip", "b.h", "sub/c.h"):
+        text = (tmp_path / name).read_text()
+        (tmp_path / name).write_text(text + "int more;\n")
+        assert pr.kernel_source_hash() != first
+        (tmp_path / name).write_text(text)
