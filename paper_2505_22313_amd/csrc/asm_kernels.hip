@@ -91,20 +91,20 @@ struct Plan {
   // (other M: about 8 points per thread, since their mixed-radix stage
   // shapes do not divide evenly among threads and need more registers each)
   static constexpr int TA = TP.ta ? TP.ta : round64(cmin(1024, cmax(64, AX * RA / (POW2 ? 16 : 8))));
-  // pass-B / B' threads: about 16 points each, 8 on the 2048 and 4096 grids
+  // pass-B / B' threads: about 16 points each, 8 on the 4096 grid
   // (passes B and B' at 4096^2: 61 -> 58 and 52 -> 48 us per wavelength)
   static constexpr int TB = TP.tb ? TP.tb : !POW2 ? round64(cmin(1024, cmax(64, BX * AY / 8)))
                             : BX * AY > 8192 ? 1024
-                            : (PID == 11 || PID == 12) ? 2 * threads_for(BX * AY)
-                                                       : threads_for(BX * AY);
-  // pass-C threads: about 16 points each, except 8 on the 2048, 4096 and
-  // 32768 grids, whose 64-, 64- and 256-row transforms spilled registers at
+                            : PID == 12 ? 2 * threads_for(BX * AY)
+                                        : threads_for(BX * AY);
+  // pass-C threads: about 16 points each, except 8 on the 4096 and
+  // 32768 grids, whose 64- and 256-row transforms spilled registers at
   // 16 (pass C at 4096^2: 71 -> 53 us per wavelength; at 32768^2: 3.84 ->
   // 3.69 ms)
   static constexpr int TC = TP.tc ? TP.tc : !POW2 ? round64(cmin(1024, cmax(64, BY * RC / 8)))
                             : BY * RC > 8192 ? 1024
-                            : (PID == 11 || PID == 12 || PID == 15) ? 2 * threads_for(BY * RC)
-                                                                     : threads_for(BY * RC);
+                            : (PID == 12 || PID == 15) ? 2 * threads_for(BY * RC)
+                                                       : threads_for(BY * RC);
   // Twiddles in LDS: omega_M^q = HI[q / S] * LO[q % S] with HI[i] = omega_M^(i S)
   // (= omega_THI^i) and LO[i] = omega_M^i.  Power-of-two M: THI = min(M, 1024),
   // which also serves every inner DFT length.  Table grids: THI = AX (S = BX),
@@ -933,6 +933,9 @@ template <int PID>
 static hipError_t launch_range(const KParams &p, int first, int last, hipStream_t s,
                                hipEvent_t *ev) {
   using P = Plan<PID>;
+  // the gradient on 3600^2 takes the small grids' passes at every size
+  constexpr bool GRAD = PID != kTab3600;
+  if (!GRAD && p.in_mode == IN_GRAD) return hipErrorInvalidValue;
   auto grid = [](long long tiles) {
     return (unsigned)(tiles < kMaxBlocks ? tiles : kMaxBlocks);
   };
@@ -948,7 +951,7 @@ static hipError_t launch_range(const KParams &p, int first, int last, hipStream_
           hipLaunchKernelGGL((k_pass_a_fwd<PID, IN_PHASE>), dim3(ga), dim3(P::TA), 0, s, p);
         else if (p.in_mode == IN_FIELD)
           hipLaunchKernelGGL((k_pass_a_fwd<PID, IN_FIELD>), dim3(ga), dim3(P::TA), 0, s, p);
-        else
+        else if constexpr (GRAD)
           hipLaunchKernelGGL((k_pass_a_fwd<PID, IN_GRAD>), dim3(ga), dim3(P::TA), 0, s, p);
         break;
       case 1: hipLaunchKernelGGL(k_pass_b_fwd<PID>, dim3(gb), dim3(P::TB), 0, s, p); break;
@@ -959,7 +962,7 @@ static hipError_t launch_range(const KParams &p, int first, int last, hipStream_
           hipLaunchKernelGGL((k_pass_a_inv<PID, OUT_PSF>), dim3(gai), dim3(P::TA), 0, s, p);
         else if (p.out_mode == OUT_FIELD)
           hipLaunchKernelGGL((k_pass_a_inv<PID, OUT_FIELD>), dim3(gai), dim3(P::TA), 0, s, p);
-        else
+        else if constexpr (GRAD)
           hipLaunchKernelGGL((k_pass_a_inv<PID, OUT_GRADH>), dim3(gai), dim3(P::TA), 0, s, p);
         break;
     }
@@ -987,9 +990,6 @@ hipError_t launch_passes(const KParams &p, int first, int last, hipStream_t s, h
   }
 }
 
-hipError_t launch_wavelength(const KParams &p, hipStream_t s, hipEvent_t *ev) {
-  return launch_passes(p, 0, kNumPasses - 1, s, ev);
-}
 static_assert(kNumTab == 14, "a launch case here or in launch_small per grid of table_plan");
 
 int plan_id(int mx, int my) {
@@ -1010,53 +1010,10 @@ int table_grids(int *rows, int *cols, int max) {
   return kNumTab;
 }
 
-template <int PID>
-static void fill_plan(PlanInfo *o) {
-  using P = Plan<PID>;
-  o->ax = P::AX; o->bx = P::BX; o->ay = P::AY; o->by = P::BY; o->ra = P::RA; o->rc = P::RC;
-  o->threads_a = P::TA; o->threads_b = P::TB; o->threads_c = P::TC;
-}
-
 // A group of wavelengths needs pass A' to hold the accumulator in registers,
 // which a radix-67 last stage (writing through a store functor) does not.
 int plan_max_group(int plan) {
-  PlanInfo o;
-  if (!plan_info(plan, &o)) return 0;
-  return o.ax % kP == 0 ? 1 : kMaxGroup;
-}
-
-bool plan_info(int plan, PlanInfo *o) {
-  switch (plan) {
-    case 4: fill_plan<4>(o); return true;
-    case 5: fill_plan<5>(o); return true;
-    case 6: fill_plan<6>(o); return true;
-    case 7: fill_plan<7>(o); return true;
-    case 8: fill_plan<8>(o); return true;
-    case 9: fill_plan<9>(o); return true;
-    case 10: fill_plan<10>(o); return true;
-    case 11: fill_plan<11>(o); return true;
-    case 12: fill_plan<12>(o); return true;
-    case 13: fill_plan<13>(o); return true;
-    case 14: fill_plan<14>(o); return true;
-    case 15: fill_plan<15>(o); return true;
-    case 16: fill_plan<16>(o); return true;
-    case 17: fill_plan<17>(o); return true;
-    case kTabBase + 0: fill_plan<kTabBase + 0>(o); return true;
-    case kTabBase + 1: fill_plan<kTabBase + 1>(o); return true;
-    case kTabBase + 2: fill_plan<kTabBase + 2>(o); return true;
-    case kTabBase + 3: fill_plan<kTabBase + 3>(o); return true;
-    case kTabBase + 4: fill_plan<kTabBase + 4>(o); return true;
-    case kTabBase + 5: fill_plan<kTabBase + 5>(o); return true;
-    case kTabBase + 6: fill_plan<kTabBase + 6>(o); return true;
-    case kTabBase + 7: fill_plan<kTabBase + 7>(o); return true;
-    case kTabBase + 8: fill_plan<kTabBase + 8>(o); return true;
-    case kTabBase + 9: fill_plan<kTabBase + 9>(o); return true;
-    case kTabBase + 10: fill_plan<kTabBase + 10>(o); return true;
-    case kTabBase + 11: fill_plan<kTabBase + 11>(o); return true;
-    case kTabBase + 12: fill_plan<kTabBase + 12>(o); return true;
-    case kTabBase + 13: fill_plan<kTabBase + 13>(o); return true;
-    default: return false;
-  }
+  return plan >= kTabBase && table_plan(plan - kTabBase).ax % kP == 0 ? 1 : kMaxGroup;
 }
 
 }  // namespace dop

@@ -735,7 +735,6 @@ dop_status dop_psf_backward(dop_context *ctx, const dop_problem *prob, const flo
       set_group_entry(kp, q, kq);
     }
     kp.first = (k == 0);
-    kp.adjoint = 1;
     kp.zl = -kp.zl;  // conj(H) = H at -z (the band limit depends on |z| only)
     kp.zl_g[0] = kp.zl;
     kp.h = h;

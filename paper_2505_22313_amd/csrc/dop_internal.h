@@ -78,7 +78,6 @@ struct KParams {
   int in_mode, out_mode;
   int full;              // 1: output the whole M x M plane (centred)
   int first;             // 1: overwrite the accumulator, 0: add to it
-  int adjoint;           // 1: adjoint pass (H conjugated through zl < 0)
   const float *h;        // heights (IN_PHASE, OUT_GRADH): row y, column x of
                          // the Ny x Nx map is h[(y >> up_log2) * nh + (x >> up_log2)]
   int up_log2;           // log2 of the nearest-neighbour upsampling factor
@@ -123,11 +122,6 @@ constexpr int kNumPasses = 5;
 // Route of an operation (by its input mode) on a valid problem (dop_api.cpp).
 Route route_of(const dop_problem *prob, InMode in);
 
-// Enqueue the five passes of one wavelength on `stream`.  If `ev` is not
-// NULL, ev[0..5] are recorded before the first pass, between passes and
-// after the last one.
-hipError_t launch_wavelength(const KParams &p, hipStream_t stream, hipEvent_t *ev);
-
 // Enqueue passes first..last (0 = A, 1 = B, 2 = C, 3 = B', 4 = A') of `p`;
 // ev (if not NULL) gets last - first + 2 marks around them.
 hipError_t launch_passes(const KParams &p, int first, int last, hipStream_t stream,
@@ -162,8 +156,8 @@ bool tri_path(int plan, int n, int rows, bool full);
 int tri_pitch(int plan, int nrows);
 hipError_t launch_tri(const KParams &p, hipStream_t s, hipEvent_t *ev);
 
-// Largest wavelength group the plan supports (1 if pass A' ends in a
-// radix-67 stage), 0 for an unknown plan.
+// Largest wavelength group of the plan's five passes (1 if pass A' ends in a
+// radix-67 stage).
 int plan_max_group(int plan);
 
 // Plan id of the My x Mx grid (mx columns, my rows): log2(M) for a square
@@ -175,14 +169,6 @@ int plan_id(int mx, int my);
 // and rectangular grids): writes up to `max` (rows, columns) pairs and
 // returns how many there are.
 int table_grids(int *rows, int *cols, int max);
-
-// Tile geometry of a pass plan (host-side copy of the compile-time plan,
-// used for reporting and tests).
-struct PlanInfo {
-  int ax, bx, ay, by, ra, rc;
-  int threads_a, threads_b, threads_c;
-};
-bool plan_info(int plan, PlanInfo *out);
 
 // Bandwidth probes (dop_probe_bandwidth): pass C's access pattern without its
 // arithmetic on the power-of-two grid of plan id `plan` (14..17), and plain

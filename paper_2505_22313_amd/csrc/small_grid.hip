@@ -155,7 +155,6 @@ __global__ __launch_bounds__(SmallPlan<PID>::TR * GR) void k_small_rows_fwd(KPar
   // element (x, b) of the tile: x fastest across threads; wavelengths in
   // planes of their own
   using G = Geo<M, RB * GR, GR == 1 ? RB : 1, GR == 1 ? 1 : M, T, true>;
-  using FS = FirstStage<G, S::REV>;
   __shared__ float2 lds[M * RB * GR];
   __shared__ float2 tw[M];
   const int nrows = p.nrows_in, n = p.n;
@@ -215,7 +214,6 @@ __global__ __launch_bounds__(SmallPlan<PID>::TR * GR) void k_small_rows_inv(KPar
   using S = SmallPlan<PID>;
   constexpr int M = S::MX, MY = S::MY, RB = S::RB, T = S::TR * GR;
   using G = Geo<M, RB * GR, GR == 1 ? RB : 1, GR == 1 ? 1 : M, T, true>;
-  using FS = FirstStage<G, false>;
   __shared__ float2 lds[M * RB * GR];
   __shared__ float2 tw[M];
   const int nrows = p.nrows_out, n = p.n;
