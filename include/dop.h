@@ -202,7 +202,9 @@ dop_status dop_psf(dop_context *ctx, const dop_problem *prob, const float *h,
  * gradient; square powers of two not while dop_profile_enable times their
  * passes); other grids when saved_u is NULL.  Grids whose x digit has the
  * factor 67 run one wavelength at a time, as do 3600^2 and the 4096 .. 16384
- * grids where they take three passes. */
+ * grids where they take three passes (a DOE of at most half of each axis in
+ * DOP_OUT_CROP; on 3600^2 also larger ones of few rows).
+ * dop_workspace_size_group gives the group and its workspace. */
 
 /*
  * dop_psf for callers that cannot allocate device memory (code under HIP

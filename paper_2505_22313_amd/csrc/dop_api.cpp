@@ -692,8 +692,10 @@ dop_status dop_psf_noalloc(dop_context *ctx, const dop_problem *prob, const floa
                 "device %d", ctx->device);
   if ((s = check_ctx_device(ctx)) != DOP_OK) return s;
   // every workspace element a pass reads has been written earlier in the same
-  // call (pass A writes the input rows, pass B every row), so the scratch
-  // left by an earlier call needs no clearing; no timing events are created
+  // call (five passes: A writes the input rows, B every row; three passes: the
+  // first writes the input rows whole, which the second reads, writing the
+  // output rows that the third reads), so the scratch left by an earlier call
+  // needs no clearing; no timing events are created
   return enqueue_psf(ctx, prob, h, amp, psf, saved_u, ctx->scratch, DOP_NOALLOC_MAX_BYTES,
                      static_cast<hipStream_t>(stream), false);
 }

@@ -23,21 +23,20 @@ namespace dop {
 //       and the optional saved field; field; or height gradient).
 // A whole row or column fits in a block, so the 2-D FFT takes two sweeps
 // instead of the large path's digit passes, and the column pass touches
-// only the N rows that hold data.  At these sizes the field (<= 32 MiB)
-// stays in the Infinity Cache between passes, and the five large-path
-// launches were latency-bound.  At 4096 the column pass, limited to two
-// columns (16-byte runs) by the LDS, was twice as slow as the large path;
-// four-column tiles fit up to 3600 rows.
+// only the N rows that hold data.  At these sizes the field (34 MB at 2048^2,
+// 104 MB at 3600^2) stays in the 256 MB Infinity Cache between passes, and the
+// five large-path launches were latency-bound.  At 4096 the column pass,
+// limited to two columns (16-byte runs) by the LDS, was twice as slow as the
+// large path; three-column tiles fit at 3600 rows.
 // ---------------------------------------------------------------------------
 // Tiles of the grids of table_plan that take the path (c = 0: the others).
 // PSF of one and of four wavelengths, gradient step of one (us per call), five
 // passes -> three: 240^2 25, 137, 55 -> 17, 22, 38; 720^2 30, 140, 65 -> 24,
 // 41, 47; 1440^2 56, 172, 112 -> 40, 88, 81; 2144^2 149, 618, 306 -> 112,
-// 457, 229; 512 x 2048 33, 135, 68 ->
-// 29, 58, 57; 5360 x 240 60, 198, 120 -> 52, 105, 105.  3600^2 takes them for
-// some operations (small_path).  3072^2 was no faster
-// (118, 443, 240 against 120, 491, 247: one 123 KB column tile per CU) and
-// keeps the five passes, as do the grids whose columns do not fit.
+// 457, 229; 512 x 2048 33, 135, 68 -> 29, 58, 57; 5360 x 240 60, 198, 120 ->
+// 52, 105, 105.  3600^2 takes them for some operations (small_path).  3072^2
+// was no faster (118, 443, 240 against 120, 491, 247: one 123 KB column tile
+// per CU) and keeps the five passes, as do the grids whose columns do not fit.
 struct SmallTab {
   int rb, tr;  // rows per S1 / S3 tile and threads (per wavelength of a group)
   int c, tc;   // columns per S2 tile and threads

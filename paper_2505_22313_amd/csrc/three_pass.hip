@@ -63,8 +63,8 @@ struct Tri {
   static constexpr int TROW = 64 * NP;                // threads of passes R and R'
   static constexpr int HALF = TROW / ROWS;            // from a thread's first item to its second
   static constexpr int TCOL = 64 * 2 * NP / NW;       // threads of pass K: a column pair
-  // Lanes and items past the end (3600: four lanes of a wavefront, 28 threads
-  // of a row's items) repeat the last one, and store what it stores.
+  // Lanes and items past the end (3600: four lanes of a wavefront, 31 threads
+  // of a row's or column's items) repeat the last one, and store what it stores.
   static constexpr bool EXACT = IW * NW == 64;
   // LDS position of element pos: one pad element per 16 keeps the first
   // exchange (stride 16) free of bank conflicts; stride 15 needs none
