@@ -24,11 +24,11 @@ KERNEL_SOURCE = os.path.join(HERE, "csrc", "asm_kernels.hip")
 CALIB_KERNEL = "__amd_rocclr_copyBuffer"
 CALIB_BYTES = 4 * 1024 ** 3
 
-COMMAND = ("rocprofv3 --pmc FETCH_SIZE --kernel-trace --output-format csv -d gpurun_out/fetch -o run -- "
+COMMAND = ("rocprofv3 --pmc FETCH_SIZE --kernel-trace --output-format csv -d counters/fetch -o run -- "
            "python3 bench.py --steps 1 --warmup 0 --no-cpu-baseline --no-serve --no-design "
            "--no-variants --lambdas 2 --calib-copy; the same with --pmc WRITE_SIZE -d "
-           "gpurun_out/write; then python -m paper_2505_22313_amd.profiling traffic "
-           "gpurun_out/fetch gpurun_out/write 32768")
+           "counters/write; then python -m paper_2505_22313_amd.profiling traffic "
+           "counters/fetch counters/write 32768")
 
 PASS_NAMES = {"k_pass_a_fwd": "pass_a_fwd", "k_pass_b_fwd": "pass_b_fwd", "k_pass_c": "pass_c",
               "k_pass_b_inv": "pass_b_inv", "k_pass_a_inv": "pass_a_inv"}
